@@ -196,7 +196,7 @@ int ent_init(const ent_config* cfg, ent_ctx** out) {
       ent::decode_partial_slots(c->decode_grid, f.max_batch, f.num_kv_heads));
   const size_t sz_acc = align_up(nslots * c->group * f.head_dim * sizeof(float));
   const size_t sz_ml = align_up(nslots * c->group * 2 * sizeof(float));
-  const size_t sz_rec = align_up(static_cast<size_t>(c->decode_grid) * 4 * sizeof(int4));
+  const size_t sz_rec = align_up(static_cast<size_t>(c->decode_grid) * 4 * sizeof(int2));
   const size_t sz_tmax = f.estimator == ENT_EST_EXACT
                              ? 0
                              : align_up(Bm * c->chunks * ent::kEstChunkThreads * sizeof(float));
@@ -232,7 +232,7 @@ int ent_init(const ent_config* cfg, ent_ctx** out) {
   c->kept_phys = reinterpret_cast<int*>(take(sz_kphys));
   c->dec_acc = reinterpret_cast<float*>(take(sz_acc));
   c->dec_ml = reinterpret_cast<float*>(take(sz_ml));
-  c->dec_rec = reinterpret_cast<int4*>(take(sz_rec));
+  c->dec_rec = reinterpret_cast<int2*>(take(sz_rec));
   c->tmax = sz_tmax ? reinterpret_cast<float*>(take(sz_tmax)) : nullptr;
   c->exbuf = sz_ex ? reinterpret_cast<float2*>(take(sz_ex)) : nullptr;
   c->tickets = reinterpret_cast<unsigned*>(take(sz_tick));

@@ -14,7 +14,7 @@
 // where it covers part of one it writes an unnormalised partial
 // (max, sum, output) to slot (range + segment), which is unique because both
 // partitions are ordered intervals.  The range in which a cut segment begins
-// also writes a record (segment, last range holding it, total units), so a
+// also writes a record (segment, last range holding it), so a
 // second kernel merges the partials of every cut segment from that record
 // alone, without rebuilding the plan.  The kept counts stay on the device.
 //
@@ -67,12 +67,11 @@ struct DecodeArgs {
   float* lse;
   float* part_acc;    // [W + S, G, D]
   float* part_ml;     // [W + S, G, 2]
-  int4* rec;          // [R] cut-segment record of each range: (segment or -1, last range, U, 0)
+  int2* rec;          // [R] cut-segment record of each range: (segment or -1, last range)
   unsigned* flags;
   int B, Hkv, G, MAXB, P;
   int W;              // waves of the decode grid
   int R;              // ranges that write partials (workgroups for bf16, waves for fp32)
-  int xw;             // 1: ranges weighted by XCD (bf16, wv_begin / wg_begin), 0: equal wave ranges
   int nsl;            // merge workgroups per segment
   float scale_log2;   // softmax scale times log2(e)
 };
@@ -137,6 +136,23 @@ __device__ __forceinline__ int range_begin(int w, int U, int W) {
 // (x + 1) W passes 2^31 once the kept units do 2^31 / W.
 __device__ __forceinline__ int wave_of(int x, int U, int W) {
   return static_cast<int>((static_cast<long long>(x + 1) * W - 1) / U);
+}
+
+// Ranges in use.  With few units the grid's ranges would be (nearly) empty,
+// and a cut segment would span many of them: the merge reads a segment's
+// pieces in rounds of kCombinePrefetch, each a memory round trip, while a
+// range's next unit is prefetched behind the one before.  So a bf16 workgroup
+// takes at least kMinUnits units (two per wave; 4, 8 and 16 measured 27.8,
+// 27.7 and 28.6 us for the step of one 2500-token request, 38.2, 33.5 and
+// 34.6 us for nine of 301-4001 tokens), and the second workgroup per CU joins
+// only once each of the first ones has kTwoUnits (16, 32 and 64: 46.8, 44.6
+// and 44.7 us for two of 12465-25000 tokens; without, 48.6).  Every range in
+// use holds a unit.  With all ranges in use those steps took 50.7, 38.9 and
+// 61.6 us, most of it in the merge.
+constexpr int kMinUnits = 8, kTwoUnits = 32;
+__device__ __forceinline__ int ranges_used(int U, int R) {
+  const int half = (R + 1) / 2;
+  return max(1, min(U < half * kTwoUnits ? half : R, (U + kMinUnits - 1) / kMinUnits));
 }
 
 // The bf16 decode's ranges, weighted by XCD: workgroups are dealt to the
@@ -268,8 +284,9 @@ __global__ __launch_bounds__(kThreads, 3) void decode_bf16_kernel(DecodeArgs a) 
   const int wave = threadIdx.x >> 6;
   const int w = blockIdx.x * kWaves + wave;
   zero_empty<D>(a, s_nk);
-  if (U == 0) {
-    if (threadIdx.x == 0) a.rec[blockIdx.x] = make_int4(-1, 0, 0, 0);
+  const int R = ranges_used(U, a.R);
+  if (U == 0 || blockIdx.x >= R) {
+    if (threadIdx.x == 0) a.rec[blockIdx.x] = make_int2(-1, 0);
     return;
   }
   const int G = a.G;
@@ -277,7 +294,7 @@ __global__ __launch_bounds__(kThreads, 3) void decode_bf16_kernel(DecodeArgs a) 
   // slot 2 i (wave i's first segment, begun before its range) and 2 i + 1
   // (its last, continuing after it): G x D sums and (max, sum) per head.
   if (lane < 2) s_cseg[2 * wave + lane] = -1;
-  const int u0 = wv_begin(w, U, a.R), u1 = wv_begin(w + 1, U, a.R);
+  const int u0 = wv_begin(w, U, R), u1 = wv_begin(w + 1, U, R);
   const int r16 = lane & 15, gq = lane >> 4;
   const int Hq = a.Hkv * G;
   const bool head_ok = r16 < G;
@@ -547,11 +564,11 @@ __global__ __launch_bounds__(kThreads, 3) void decode_bf16_kernel(DecodeArgs a) 
       const int seg_start = s_pref[b] + g * s_nk[b];
       const int seg_end = seg_start + s_nk[b];
       const int wg = blockIdx.x;
-      const int g0 = wg_begin(wg, U, a.R), g1 = wg_begin(wg + 1, U, a.R);
+      const int g0 = wg_begin(wg, U, R), g1 = wg_begin(wg + 1, U, R);
       const bool whole = seg_start >= g0 && seg_end <= g1;
       const bool own = !whole && seg_start >= g0;
       s_gd[rank] = make_int4(k | (j << 8) | (whole ? 1 << 16 : 0) | (own ? 1 << 17 : 0), seg,
-                             own ? wg_of(seg_end - 1, U, a.R) : 0, 0);
+                             own ? wg_of(seg_end - 1, U, R) : 0, 0);
     }
     if (k == 0) s_ng = ng;
   }
@@ -600,7 +617,7 @@ __global__ __launch_bounds__(kThreads, 3) void decode_bf16_kernel(DecodeArgs a) 
       }
     }
   }
-  if (threadIdx.x == 0) a.rec[wg] = make_int4(owner, owner_last, U, 0);
+  if (threadIdx.x == 0) a.rec[wg] = make_int2(owner, owner_last);
 }
 
 template <int D>
@@ -618,9 +635,10 @@ __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
   zero_empty<D>(a, s_nk);
   // This wave's record; replaced below (same lane, program order) when a
   // segment that begins in its range is cut.
-  if (lane == 0) a.rec[w] = make_int4(-1, 0, 0, 0);
-  if (U == 0) return;
-  const int u0 = range_begin(w, U, a.W), u1 = range_begin(w + 1, U, a.W);
+  if (lane == 0) a.rec[w] = make_int2(-1, 0);
+  const int W = min(a.W, U);            // a unit to each wave in use, at least
+  if (U == 0 || w >= W) return;
+  const int u0 = range_begin(w, U, W), u1 = range_begin(w + 1, U, W);
   if (u0 >= u1) return;
   const int t16 = lane & 15, hs = lane >> 4;
   const int G = a.G;
@@ -653,7 +671,7 @@ __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
           a.lse[oh] = l_run[h] > 0.f ? (m_run[h] + log2f(l_run[h])) * kLn2 : -INFINITY;
       } else {
         if (h == 0 && lane == 0 && seg_start >= u0)
-          a.rec[w] = make_int4(cur_seg, wave_of(seg_end - 1, U, a.W), U, 0);
+          a.rec[w] = make_int2(cur_seg, wave_of(seg_end - 1, U, W));
 #pragma unroll
         for (int y = 0; y < DPL; ++y) a.part_acc[(slot * G + h) * D + lane + 64 * y] = o[h][y];
         if (lane == 0) {
@@ -749,17 +767,17 @@ __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
 // 16-byte load), in range order, with a running (max, sum, output) rescaled
 // as the maximum grows; the loads of eight partials are issued together, so
 // one memory round trip follows the record for segments cut into at most
-// eight pieces.  Ranges with no units (fewer units than ranges) wrote no
-// partial.
+// eight pieces.  Every range between them holds units, so all wrote a partial
+// (testing that cost two 64-bit divisions a piece: 2 us of the nine-request
+// step's 33.5, 9 us of 58 for two requests of 12465-25000 tokens).
 constexpr int kCombinePrefetch = 8;        // partials whose loads are issued together
 
 template <int D>
 __device__ __forceinline__ void combine_body(const DecodeArgs& a, int item) {
   const int range = item / a.nsl, slice = item - range * a.nsl;
-  const int4 rec = a.rec[range];
+  const int2 rec = a.rec[range];
   const int seg = rec.x;
   if (seg < 0) return;                       // no cut segment begins in this range
-  const int U = rec.z;
   const int w0 = range, w1 = rec.y;
   const int G = a.G;
   const int b = seg / a.Hkv, g = seg % a.Hkv;
@@ -776,8 +794,7 @@ __device__ __forceinline__ void combine_body(const DecodeArgs& a, int item) {
 #pragma unroll
     for (int k = 0; k < kCombinePrefetch; ++k) {
       const int wi = c0 + k;
-      const bool ok = wi <= w1 && (a.xw ? wg_begin(wi + 1, U, a.R) > wg_begin(wi, U, a.R)
-                                        : range_begin(wi + 1, U, a.R) > range_begin(wi, U, a.R));
+      const bool ok = wi <= w1;
       const long long slot = static_cast<long long>(wi) + seg;
       m[k] = ok ? a.part_ml[(slot * G + r) * 2 + 0] : -INFINITY;
       l[k] = ok ? a.part_ml[(slot * G + r) * 2 + 1] : 0.f;
@@ -905,7 +922,6 @@ hipError_t launch_decode(const ent_ctx* c, int B, const void* q, const void* k_c
   a.P = cf.num_pool_blocks;
   a.W = c->decode_grid * kWaves;
   a.R = cf.kv_dtype == ENT_BF16 ? c->decode_grid : a.W;
-  a.xw = cf.kv_dtype == ENT_BF16 ? 1 : 0;
   a.scale_log2 = cf.scale * kLog2e;
   const size_t lds = plan_lds_bytes(B);
   const dim3 grid(c->decode_grid);

@@ -77,7 +77,7 @@ struct ent_ctx {
   int* kept_phys = nullptr;       // [max_batch, MAXB]  physical blocks of the kept lists
   float* dec_acc = nullptr;       // [decode partial slots, G, d]
   float* dec_ml = nullptr;        // [decode partial slots, G, 2]
-  int4* dec_rec = nullptr;        // [decode waves]  cut-segment records of the decode ranges
+  int2* dec_rec = nullptr;        // [decode waves]  cut-segment records of the decode ranges
   float* tmax = nullptr;          // [max_batch, chunks, 256]  per-thread logit maxima (estimators)
   float2* exbuf = nullptr;        // [max_batch, MAXB, H_q]  exact mode: (log mass, mean logit) per block
   unsigned* tickets = nullptr;    // [max_batch]  per-sequence counters of the fused step (zero between launches)
