@@ -763,58 +763,81 @@ __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
 // record names the cut segment that begins in it, if any, and the last range
 // holding a piece of it; a.nsl slices of at most 256 groups of four outputs
 // per segment.  Each thread merges four consecutive outputs of one head row
-// on its own (a partial's max and sum loaded once, its four sums as one
-// 16-byte load), in range order, with a running (max, sum, output) rescaled
-// as the maximum grows; the loads of eight partials are issued together, so
-// one memory round trip follows the record for segments cut into at most
-// eight pieces.  Every range between them holds units, so all wrote a partial
-// (testing that cost two 64-bit divisions a piece: 2 us of the nine-request
-// step's 33.5, 9 us of 58 for two requests of 12465-25000 tokens).
-constexpr int kCombinePrefetch = 8;        // partials whose loads are issued together
+// (a partial's max and sum loaded once, its four sums as one 16-byte load),
+// in range order; the loads of kCombinePrefetch partials are issued together,
+// so one memory round trip follows the record for segments cut into at most
+// that many pieces.  Past that, where the outputs leave threads idle (G d
+// under 1024), groups of threads take a part of the pieces each and merge
+// through LDS: the step of two requests of 24941-126661 tokens (16/4 heads
+// of 64 dims, 64 pieces a segment) took 64.7 us against 80.2 with one group
+// and eight partials at a time, the fp32 tiny step (16 groups) 32.5 against
+// 34.4, three requests of 14616-21096 tokens 58.9 against 61.9; the 8B step
+// and the 70B-shaped loop, few pieces a segment, are unchanged.  Every range
+// between the first and the last holds units, so all wrote a partial (testing
+// that cost two 64-bit divisions a piece: 2 us of the nine-request step's
+// 33.5, 9 us of 58 for two requests of 12465-25000 tokens).
+constexpr int kCombinePrefetch = 16;       // partials whose loads are issued together
+
+// Running (max, sum, outputs) with a partial or another running triple added.
+__device__ __forceinline__ void combine_add(float& M, float& L, f32x4_t& acc, float m, float l,
+                                            f32x4_t v) {
+  if (!(l > 0.f)) return;
+  const float Mn = fmaxf(M, m);
+  const float f_old = (M == -INFINITY) ? 0.f : exp2f(M - Mn);
+  const float f_new = exp2f(m - Mn);
+  L = L * f_old + l * f_new;
+  acc = acc * f_old + v * f_new;
+  M = Mn;
+}
 
 template <int D>
 __device__ __forceinline__ void combine_body(const DecodeArgs& a, int item) {
+  __shared__ __attribute__((aligned(16))) f32x4_t s_acc[kThreads];
+  __shared__ float2 s_ml[kThreads];
   const int range = item / a.nsl, slice = item - range * a.nsl;
   const int2 rec = a.rec[range];
   const int seg = rec.x;
   if (seg < 0) return;                       // no cut segment begins in this range
-  const int w0 = range, w1 = rec.y;
-  const int G = a.G;
-  const int b = seg / a.Hkv, g = seg % a.Hkv;
-  const int Hq = a.Hkv * G;
-  const int q4 = slice * kThreads + static_cast<int>(threadIdx.x);   // group of four outputs
-  if (q4 >= G * D / 4) return;
+  const int G = a.G, t = threadIdx.x;
+  const int pieces = rec.y - range + 1;
+  const int n4 = G * D / 4;                  // groups of four outputs (a power of two)
+  const int ng = pieces > kCombinePrefetch && n4 < kThreads ? kThreads / n4 : 1;
+  const int gi = ng > 1 ? t / n4 : 0;
+  const int q4 = ng > 1 ? t - gi * n4 : slice * kThreads + t;
+  if (q4 >= n4) return;                      // (ng = 1: no barrier follows)
+  const int per = (pieces + ng - 1) / ng;
+  const int p0 = range + gi * per, p1 = min(p0 + per, rec.y + 1);
   const int r = (4 * q4) / D, d = 4 * q4 - r * D;
-  const long long ob = static_cast<long long>(b) * Hq + g * G;   // first output head row
   float M = -INFINITY, L = 0.f;
   f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-  for (int c0 = w0; c0 <= w1; c0 += kCombinePrefetch) {
-    float m[kCombinePrefetch], l[kCombinePrefetch];
+  for (int c0 = p0; c0 < p1; c0 += kCombinePrefetch) {
+    float2 ml[kCombinePrefetch];
     f32x4_t v[kCombinePrefetch];
 #pragma unroll
     for (int k = 0; k < kCombinePrefetch; ++k) {
-      const int wi = c0 + k;
-      const bool ok = wi <= w1;
-      const long long slot = static_cast<long long>(wi) + seg;
-      m[k] = ok ? a.part_ml[(slot * G + r) * 2 + 0] : -INFINITY;
-      l[k] = ok ? a.part_ml[(slot * G + r) * 2 + 1] : 0.f;
-      v[k] = ok ? *reinterpret_cast<const f32x4_t*>(a.part_acc + (slot * G + r) * D + d)
+      const bool ok = c0 + k < p1;
+      const long long row = (static_cast<long long>(c0 + k) + seg) * G + r;
+      ml[k] = ok ? *reinterpret_cast<const float2*>(a.part_ml + row * 2) : make_float2(-INFINITY, 0.f);
+      v[k] = ok ? *reinterpret_cast<const f32x4_t*>(a.part_acc + row * D + d)
                 : f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
 #pragma unroll
-    for (int k = 0; k < kCombinePrefetch; ++k) {
-      if (!(l[k] > 0.f)) continue;
-      const float Mn = fmaxf(M, m[k]);
-      const float f_old = (M == -INFINITY) ? 0.f : exp2f(M - Mn);
-      const float f_new = exp2f(m[k] - Mn);
-      L = L * f_old + l[k] * f_new;
-      acc = acc * f_old + v[k] * f_new;
-      M = Mn;
+    for (int k = 0; k < kCombinePrefetch; ++k) combine_add(M, L, acc, ml[k].x, ml[k].y, v[k]);
+  }
+  if (ng > 1) {
+    s_acc[t] = acc;
+    s_ml[t] = make_float2(M, L);
+    __syncthreads();
+    if (gi != 0) return;
+    for (int k = 1; k < ng; ++k) {
+      const float2 ml = s_ml[k * n4 + q4];
+      combine_add(M, L, acc, ml.x, ml.y, s_acc[k * n4 + q4]);
     }
   }
+  const long long oh = static_cast<long long>(seg) * G + r;    // b H_q + g G + r
   const f32x4_t res = L > 0.f ? acc / L : f32x4_t{0.f, 0.f, 0.f, 0.f};
-  *reinterpret_cast<f32x4_t*>(a.out + (ob + r) * D + d) = res;
-  if (d == 0 && a.lse) a.lse[ob + r] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
+  *reinterpret_cast<f32x4_t*>(a.out + oh * D + d) = res;
+  if (d == 0 && a.lse) a.lse[oh] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
 }
 
 template <int D>
