@@ -196,13 +196,11 @@ __device__ __forceinline__ sf32x2_t score_head_compute(
     l[e] = ok ? z + ((j == nb - 1) ? ln_last : ln_full) : -INFINITY;
     m = fmaxf(m, l[e]);
   }
-  m = fmaxf(m, __shfl_xor(m, 16));
-  m = fmaxf(m, __shfl_xor(m, 32));
+  m = xor_max<32>(xor_max<16>(m));
   float sum = 0.f;
 #pragma unroll
   for (int e = 0; e < 4; ++e) sum += (l[e] == -INFINITY) ? 0.f : expf(l[e] - m);
-  sum += __shfl_xor(sum, 16);
-  sum += __shfl_xor(sum, 32);
+  sum = xor_add<32>(xor_add<16>(sum));
   if (gq == 0 && r16 < G) {
     float* lp = lse_part + ((static_cast<long long>(b) * nch_max + ch) * Hq + g * G + r16) * 2;
     lp[0] = m;
@@ -229,22 +227,30 @@ __device__ __forceinline__ void store_held_z(sf32x2_t v, float* __restrict__ zbu
   if (jt + e0 + 1 < nb) zrow[(e0 + 1) * Hq] = v.y;
 }
 
-template <int G, int L>
+// Sum of each of G values over the L lanes of a group by a halving butterfly:
+// lane li ends with the sum of value li / (L / G).
+template <int S>
+__device__ __forceinline__ float xor_get(float v) {
+  return __uint_as_float(xor_lane<S>(__float_as_uint(v)));
+}
+template <int G, int L, int N = G, int S = L / 2>
 __device__ __forceinline__ float reduce_heads(float (&a)[G], int li) {
+  if constexpr (N > 1) {
+    const bool up = (li & S) != 0;
 #pragma unroll
-  for (int n = G, s = L / 2; n > 1; n >>= 1, s >>= 1) {
-    const bool up = (li & s) != 0;
-#pragma unroll
-    for (int i = 0; i < n / 2; ++i) {
-      const float keep = up ? a[i + n / 2] : a[i];
-      const float send = up ? a[i] : a[i + n / 2];
-      a[i] = keep + __shfl_xor(send, s);
+    for (int i = 0; i < N / 2; ++i) {
+      const float keep = up ? a[i + N / 2] : a[i];
+      const float send = up ? a[i] : a[i + N / 2];
+      a[i] = keep + xor_get<S>(send);
     }
+    return reduce_heads<G, L, N / 2, S / 2>(a, li);
+  } else {
+    if constexpr (S >= 1) {
+      a[0] += xor_get<S>(a[0]);
+      return reduce_heads<G, L, 1, S / 2>(a, li);
+    }
+    return a[0];
   }
-  float v = a[0];
-#pragma unroll
-  for (int s = L / (2 * G); s >= 1; s >>= 1) v += __shfl_xor(v, s);
-  return v;
 }
 
 // smem: q [Hq][D] fp32, then z tile [kValuChunk][Hq].
@@ -282,7 +288,7 @@ __device__ __forceinline__ void score_valu_body(
   const int nfl = Hkv * D;
   const int np = (nfl + 255) >> 8;
   for (int blk = 0; blk < nmine; ++blk) {
-    const int p = __shfl(my_p, blk);
+    const int p = lane_at(my_p, blk);
     for (int k = 0; k < np; ++k) {
       const int f = 256 * k + 4 * lane;
       const bool gv = f < nfl;
@@ -491,8 +497,8 @@ __device__ __forceinline__ float score_term(float z, float lnn, float L) {
 // LPB is 1, 2 or 4: constant offsets (cheap cross-lane moves), the levels
 // past LPB skipped uniformly.
 __device__ __forceinline__ float lanes_sum(float acc, int LPB) {
-  if (LPB > 1) acc += __shfl_xor(acc, 1);
-  if (LPB > 2) acc += __shfl_xor(acc, 2);
+  if (LPB > 1) acc = xor_add<1>(acc);
+  if (LPB > 2) acc = xor_add<2>(acc);
   return acc;
 }
 
@@ -666,12 +672,8 @@ __device__ __forceinline__ void select_core(unsigned* keys, const int* tbl, int 
       const unsigned c0 = sh.hist[4 * lane], c1 = sh.hist[4 * lane + 1],
                      c2 = sh.hist[4 * lane + 2], c3 = sh.hist[4 * lane + 3];
       const unsigned cl = c0 + c1 + c2 + c3;
-      unsigned suf = cl;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const unsigned n = __shfl_down(suf, o);
-        if (lane + o < 64) suf += n;
-      }
+      const unsigned incl = wave_scan_u(cl);
+      const unsigned suf = lane_at(static_cast<int>(incl), 63) - incl + cl;
       const unsigned krem = static_cast<unsigned>(sh.krem);
       const unsigned above = suf - cl;       // keys in higher lanes' bins
       if (above < krem && suf >= krem) {

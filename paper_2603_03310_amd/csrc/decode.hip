@@ -94,12 +94,7 @@ __device__ void build_plan(const DecodeArgs& a, int* s_pref, int* s_nk, int* s_N
       loc += nk * a.Hkv;
     }
   }
-  int incl = loc;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int n = __shfl_up(incl, o);
-    if (lane >= o) incl += n;
-  }
+  const int incl = static_cast<int>(wave_scan_u(static_cast<unsigned>(loc)));
   if (lane == 63) s_red[wave] = incl;
   __syncthreads();
   int run = incl - loc;
@@ -309,8 +304,8 @@ __global__ __launch_bounds__(kThreads, 3) void decode_bf16_kernel(DecodeArgs a) 
   bf16x8_t kcur[KS], knxt[KS];
   s16x4_t vcur[MT], vnxt[MT];
   auto load_tiles = [&](int i, bf16x8_t (&kr)[KS], s16x4_t (&vr)[MT]) {
-    const int seg = __shfl(win.seg, i);
-    const int p = max(__shfl(win.p, i), 0);
+    const int seg = lane_at(win.seg, i);
+    const int p = max(lane_at(win.p, i), 0);
     const int g = max(seg, 0) % a.Hkv;
     const long long tile = (static_cast<long long>(p) * a.Hkv + g) * kBlock * D;
     // K: load ks covers the tile's bytes [ks, ks + 1) * 4 KB / KS whole (lane
@@ -330,7 +325,7 @@ __global__ __launch_bounds__(kThreads, 3) void decode_bf16_kernel(DecodeArgs a) 
   for (int m = 0; m < MT; ++m) oacc[m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   // The first segment's queries load together with the first tiles.
   if (busy) {
-    cur_seg = __shfl(win.seg, 0);
+    cur_seg = lane_at(win.seg, 0);
     const int b = cur_seg / a.Hkv, g = cur_seg % a.Hkv;
     const long long qh = static_cast<long long>(b) * Hq + g * G + r16;
 #pragma unroll
@@ -341,8 +336,7 @@ __global__ __launch_bounds__(kThreads, 3) void decode_bf16_kernel(DecodeArgs a) 
   }
 
   auto flush = [&]() {
-    float l_tot = l_run + __shfl_xor(l_run, 16);
-    l_tot += __shfl_xor(l_tot, 32);
+    const float l_tot = xor_add<32>(xor_add<16>(l_run));
     const int b = cur_seg / a.Hkv, g = cur_seg % a.Hkv;
     const int seg_start = s_pref[b] + g * s_nk[b];
     const int seg_end = seg_start + s_nk[b];
@@ -383,7 +377,7 @@ __global__ __launch_bounds__(kThreads, 3) void decode_bf16_kernel(DecodeArgs a) 
       win = unit_meta(a, ubase + lane, u1, s_pref, s_nk, s_N);
       load_tiles(0, kc, vc);
     }
-    const int seg = __shfl(win.seg, i);
+    const int seg = lane_at(win.seg, i);
     if (seg != cur_seg) {
       if (cur_seg >= 0) flush();
       cur_seg = seg;
@@ -403,8 +397,8 @@ __global__ __launch_bounds__(kThreads, 3) void decode_bf16_kernel(DecodeArgs a) 
     // covers only the current unit's loads; past the end of the window or of
     // the range the current tiles are re-read (cache hits) and discarded.
     load_tiles((i + 1 < kWindow && u + 1 < u1) ? i + 1 : i, kn, vn);
-    const int p = __shfl(win.p, i);
-    const int nv = __shfl(win.nv, i);
+    const int p = lane_at(win.p, i);
+    const int nv = lane_at(win.nv, i);
     if (p >= 0) {
       // The K tile through the wave's LDS rows: written as loaded (whole
       // rows per load), read back with lane (r16, gq) holding row r16, MFMA
@@ -441,8 +435,7 @@ __global__ __launch_bounds__(kThreads, 3) void decode_bf16_kernel(DecodeArgs a) 
       // The running max moves only when some score exceeds it.
       if (__any(up)) {
         float mloc = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+        mloc = xor_max<32>(xor_max<16>(mloc));
         const float m_new = fmaxf(m_run, mloc);
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
         l_run *= alpha;
@@ -689,7 +682,7 @@ __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
       i = 0;
       win = unit_meta(a, ubase + lane, u1, s_pref, s_nk, s_N);
     }
-    const int seg = __shfl(win.seg, i);
+    const int seg = lane_at(win.seg, i);
     if (seg != cur_seg) {
       if (cur_seg >= 0) flush();
       cur_seg = seg;
@@ -703,8 +696,8 @@ __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
         for (int y = 0; y < DPL; ++y) o[h][y] = 0.f;
       }
     }
-    const int p = __shfl(win.p, i);
-    const int nv = __shfl(win.nv, i);
+    const int p = lane_at(win.p, i);
+    const int nv = lane_at(win.nv, i);
     if (p < 0) continue;
     const long long tile = (static_cast<long long>(p) * a.Hkv + (seg % a.Hkv)) * kBlock * D;
     // Scores: lane (t16, hs) takes token t16 for heads hs, hs+4, hs+8, hs+12.
@@ -733,7 +726,7 @@ __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
       float mb = -INFINITY;
 #pragma unroll
       for (int tt = 0; tt < kBlock; ++tt) {
-        st[tt] = __shfl(sc[h >> 2], 16 * (h & 3) + tt);
+        st[tt] = lane_at(sc[h >> 2], 16 * (h & 3) + tt);
         mb = fmaxf(mb, st[tt]);
       }
       const float m_new = fmaxf(m_run[h], mb);

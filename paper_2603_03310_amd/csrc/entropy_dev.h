@@ -201,12 +201,7 @@ __device__ __forceinline__ float controller_update(int b, float H, float T, floa
 // Exclusive prefix sum (float64) over the first kSampleThreads threads.
 __device__ __forceinline__ double block_excl_scan_d(double v, double* wsum) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  double incl = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const double n = __shfl_up(incl, o);
-    if (lane >= o) incl += n;
-  }
+  const double incl = wave_scan_d(v);
   if (lane == 63 && w < kSampleThreads / 64) wsum[w] = incl;
   __syncthreads();
   double before = 0.0;
@@ -265,13 +260,8 @@ __device__ __forceinline__ int sample_body(const float* __restrict__ logits, lon
     double loc = 0.0;
 #pragma unroll
     for (int k = 0; k < PER; ++k) loc += wl[k];
-    double incl = loc;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const double n = __shfl_up(incl, o);
-      if (t >= o) incl += n;
-    }
-    const double tot = __shfl(incl, 63);
+    const double incl = wave_scan_d(loc);
+    const double tot = lane_at(incl, 63);
     const double target = static_cast<double>(u) * tot;
     // The lane's running mass, stepped chunk by chunk from its exclusive prefix.
     double cum = incl - loc, run = cum;

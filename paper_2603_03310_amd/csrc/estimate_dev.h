@@ -112,8 +112,7 @@ __device__ __forceinline__ float est_block_sum(float v, EstShared& sh, int slot)
 // Integer sum over the whole workgroup (result in every thread).
 __device__ __forceinline__ int est_block_count(int v, EstShared& sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  v = static_cast<int>(wave_sum_u(static_cast<unsigned>(v)));
   if (lane == 0) sh.ired[wave] = v;
   __syncthreads();
   int r = 0;
@@ -218,12 +217,8 @@ __device__ __forceinline__ unsigned est_kth_largest(const Src& src, int n4, unsi
           c[j + 3] = h.w;
           cl += h.x + h.y + h.z + h.w;
         }
-        unsigned suf = cl;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const unsigned nx = __shfl_down(suf, o);
-          if (lane + o < 64) suf += nx;
-        }
+        const unsigned incl = wave_scan_u(cl);
+        const unsigned suf = lane_at(static_cast<int>(incl), 63) - incl + cl;
         const unsigned krem = static_cast<unsigned>(sh.krem);
         const unsigned above = suf - cl;
         if (above < krem && suf >= krem) {
@@ -309,12 +304,7 @@ __device__ __forceinline__ int est_qualifying(const Src& src, int n1, unsigned t
       const int r = lane * per + i;
       if (r < nrun) loc += sh.hist[r];
     }
-    unsigned incl = loc;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const unsigned nx = __shfl_up(incl, o);
-      if (lane >= o) incl += nx;
-    }
+    const unsigned incl = wave_scan_u(loc);
     unsigned run = incl - loc;
     for (int i = 0; i < per; ++i) {
       const int r = lane * per + i;

@@ -166,8 +166,7 @@ __global__ __launch_bounds__(kExThreads) void exact_score_bf16_kernel(ExactArgs 
       s[e] = acc[e] * a.scale;
       if (4 * gq + e < nv) m = fmaxf(m, s[e]);
     }
-    m = fmaxf(m, __shfl_xor(m, 16));
-    m = fmaxf(m, __shfl_xor(m, 32));
+    m = xor_max<32>(xor_max<16>(m));
     float S = 0.f, W = 0.f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -177,10 +176,8 @@ __global__ __launch_bounds__(kExThreads) void exact_score_bf16_kernel(ExactArgs 
         W += w * s[e];
       }
     }
-    S += __shfl_xor(S, 16);
-    S += __shfl_xor(S, 32);
-    W += __shfl_xor(W, 16);
-    W += __shfl_xor(W, 32);
+    S = xor_add<32>(xor_add<16>(S));
+    W = xor_add<32>(xor_add<16>(W));
     const float l = m + logf(S);
     if (gq == 0 && r16 < G)
       a.ex[(static_cast<long long>(b) * a.MAXB + j) * Hq + g * G + r16] = make_float2(l, W / S);
@@ -241,15 +238,11 @@ __global__ __launch_bounds__(kExThreads) void exact_score_f32_kernel(ExactArgs a
       const bool ok = tok < nv;
       const float s = dot * a.scale;
       float m = ok ? s : -INFINITY;
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+      m = xor_max<8>(xor_max<4>(xor_max<2>(xor_max<1>(m))));
       const float w = ok ? expf(s - m) : 0.f;
       float S = w, W = ok ? w * s : 0.f;
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) {
-        S += __shfl_xor(S, o);
-        W += __shfl_xor(W, o);
-      }
+      S = xor_add<8>(xor_add<4>(xor_add<2>(xor_add<1>(S))));
+      W = xor_add<8>(xor_add<4>(xor_add<2>(xor_add<1>(W))));
       const float l = m + logf(S);
       if (tok == 0 && h < G) {
         a.ex[(static_cast<long long>(b) * a.MAXB + j) * Hq + g * G + h] = make_float2(l, W / S);
@@ -293,8 +286,7 @@ __global__ __launch_bounds__(kRowThreads) void exact_block_score_kernel(
       acc += expf(e.x - sL[h]) * (sL[h] - e.y);
     }
   }
-  acc += __shfl_xor(acc, 1);
-  acc += __shfl_xor(acc, 2);
+  acc = xor_add<2>(xor_add<1>(acc));
   if (j < nb && qq == 0) scores[static_cast<long long>(b) * MAXB + j] = __fdiv_rn(acc, static_cast<float>(Hq));
 }
 

@@ -56,12 +56,7 @@ __device__ void tile_plan(const int* __restrict__ ctx_lens, int B, int MAXB, int
       loc += ok ? (N + kBlock * kMfmaChunk - 1) / (kBlock * kMfmaChunk) : 0;
     }
   }
-  int incl = loc;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int n = __shfl_up(incl, o);
-    if (lane >= o) incl += n;
-  }
+  const int incl = static_cast<int>(wave_scan_u(static_cast<unsigned>(loc)));
   if (lane == 63) s_red[wave] = incl;
   __syncthreads();
   int run = incl - loc;

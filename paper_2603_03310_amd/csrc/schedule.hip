@@ -142,15 +142,7 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(SchedArgs a) {
         le += ceq[r];
       }
     }
-    unsigned ig = lg, ie = le;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const unsigned ng = __shfl_up(ig, o), ne = __shfl_up(ie, o);
-      if (lane >= o) {
-        ig += ng;
-        ie += ne;
-      }
-    }
+    const unsigned ig = wave_scan_u(lg), ie = wave_scan_u(le);
     unsigned rg = ig - lg, re = ie - le;
     for (int j = 0; j < per; ++j) {
       const int r = lane * per + j;
