@@ -620,10 +620,29 @@ __device__ __forceinline__ int encode_phys(int p, int j, int nb, int P) {
 // The k-th largest of nb keys in LDS by the whole workgroup: a radix select
 // over the bits in which the keys differ, 8 at a time from the top (the
 // common leading bits are the prefix already); once at most kSelRankMax keys
-// share the prefix, the answer is found among them by counting ranks.
+// share the prefix, the answer is found among them by counting ranks.  With
+// no more keys than that, the ranks alone (the fp32 tiny step, up to 32
+// blocks, 30.4 -> 29.8 us with the controller's state loaded early; ranking
+// up to 192 or 512 blocks so was no faster than the radix select at 157 and
+// slower at 300-500).
 __device__ __forceinline__ unsigned radix_kth_largest(const unsigned* keys, int nb, int k,
                                                       SelectShared& sh) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  if (nb <= kSelRankMax) {
+    // One key per thread, which counts the keys above it and at or above it.
+    const unsigned v = t < nb ? keys[t] : 0u;
+    if (wave == 0) {
+      int gt = 0, ge = 0;
+#pragma unroll 4
+      for (int i = 0; i < nb; ++i) {
+        gt += keys[i] > v;
+        ge += keys[i] >= v;
+      }
+      if (t < nb && gt < k && ge >= k) sh.rv = v;   // equal keys write the same value
+    }
+    __syncthreads();
+    return sh.rv;
+  }
   unsigned kmin = 0xFFFFFFFFu, kmax = 0u;
 #pragma unroll 4
   for (int i = t; i < nb; i += kSelThreads) {

@@ -19,9 +19,9 @@ __global__ __launch_bounds__(kEstFinalizeThreads) void estimate_finalize_kernel(
   extern __shared__ __attribute__((aligned(16))) unsigned est_lds[];
   __shared__ EstShared esh;
   const int b = blockIdx.x;
-  const float T = temp[b];
-  const float H = row_estimate(est, k, part, tmax, logits, ld, V, C, T * t_cal, b, est_lds, esh);
-  if (threadIdx.x == 0) controller_update(b, H, T, h_prev, tau, temp, h_out, temp_used, ct);
+  const ControlState cs = controller_load(b, h_prev, tau, temp);
+  const float H = row_estimate(est, k, part, tmax, logits, ld, V, C, cs.T * t_cal, b, est_lds, esh);
+  if (threadIdx.x == 0) controller_update(b, H, cs, h_prev, tau, temp, h_out, temp_used, ct);
 }
 
 // One wave per row: merge of the row's chunk triples, then the controller.
@@ -31,8 +31,9 @@ __global__ __launch_bounds__(256) void entropy_finalize_kernel(
     float* __restrict__ temp_used, Control ct) {
   const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (b >= B) return;
+  const ControlState cs = controller_load(b, h_prev, tau, temp);
   const float H = row_entropy(part, C, b);
-  if ((threadIdx.x & 63) == 0) controller_update(b, H, temp[b], h_prev, tau, temp, h_out, temp_used, ct);
+  if ((threadIdx.x & 63) == 0) controller_update(b, H, cs, h_prev, tau, temp, h_out, temp_used, ct);
 }
 
 template <bool VEC>

@@ -143,15 +143,25 @@ __device__ __forceinline__ void entropy_chunk_body(const float* __restrict__ log
   }
 }
 
-// Entropy of row b from its C chunk triples, by one wave (result in every lane).
+// Entropy of row b from its C chunk triples, by one wave (result in every
+// lane).  A lane's first triple is loaded whole: up to 64 chunks (262144
+// logits) the merge is one memory round trip.
 __device__ __forceinline__ float row_entropy(const float* __restrict__ part, int C, int b) {
   const int lane = threadIdx.x & 63;
   const float* pr = part + static_cast<long long>(b) * C * 3;
-  float mloc = -INFINITY;
-  for (int i = lane; i < C; i += 64) mloc = fmaxf(mloc, pr[3 * i]);
+  const int i0 = min(lane, C - 1);
+  const float m0 = pr[3 * i0], s0 = lane < C ? pr[3 * i0 + 1] : 0.f, w0 = pr[3 * i0 + 2];
+  float mloc = m0;
+  for (int i = lane + 64; i < C; i += 64) mloc = fmaxf(mloc, pr[3 * i]);
   const float MG = wave_max(mloc);
   float s = 0.f, w = 0.f;
-  for (int i = lane; i < C; i += 64) {
+  if (s0 > 0.f) {
+    const float dm = m0 - MG;
+    const float f = exp2f(dm);
+    s = s0 * f;
+    w = f * (w0 + s0 * dm);
+  }
+  for (int i = lane + 64; i < C; i += 64) {
     const float mc = pr[3 * i];
     const float sc = pr[3 * i + 1];
     const float wc = pr[3 * i + 2];
@@ -172,25 +182,35 @@ __device__ __forceinline__ float row_entropy(const float* __restrict__ part, int
   }
 }
 
+// The controller's state of sequence b, loaded before its entropy is formed
+// so that the update waits for no memory.
+struct ControlState {
+  float T, h_prev, tau;
+};
+__device__ __forceinline__ ControlState controller_load(int b, const float* h_prev, const float* tau,
+                                                        const float* temp) {
+  return ControlState{temp[b], h_prev[b], tau[b]};
+}
+
 // Controller update of sequence b given its entropy H (or estimate) at its
-// controlled temperature T (temp_used nullable: the fused step records T_t
+// controlled temperature cs.T (temp_used nullable: the fused step records T_t
 // earlier).  The controller acts on H + h_bias (0 outside stress tests); the
 // temperature's multiplicative step exp(eta (H - H*)) is clipped to
 // [e^-rho_t, e^rho_t] (no-op for rho_t = inf) before the clip to
 // [T_min, T_max].  Returns the entropy acted on (the budget's input).
-__device__ __forceinline__ float controller_update(int b, float H, float T, float* h_prev,
-                                                   float* tau, float* temp, float* h_out,
-                                                   float* temp_used, const Control& ct) {
+__device__ __forceinline__ float controller_update(int b, float H, const ControlState& cs,
+                                                   float* h_prev, float* tau, float* temp,
+                                                   float* h_out, float* temp_used,
+                                                   const Control& ct) {
 #pragma clang fp contract(off)
   H = H + ct.h_bias;
   h_out[b] = H;
-  if (temp_used) temp_used[b] = T;
-  const float hp = h_prev[b];
-  float ta = tau[b];
-  if (!isnan(hp)) ta += fmaxf(0.f, hp - H);
+  if (temp_used) temp_used[b] = cs.T;
+  float ta = cs.tau;
+  if (!isnan(cs.h_prev)) ta += fmaxf(0.f, cs.h_prev - H);
   float step = expf(ct.eta * (H - ct.h_target));
   step = fminf(fmaxf(step, expf(-ct.rho_t)), expf(ct.rho_t));
-  float tn = T * step;
+  float tn = cs.T * step;
   tn = fminf(fmaxf(tn, ct.t_min), ct.t_max);
   tau[b] = ta;
   h_prev[b] = H;

@@ -31,6 +31,15 @@
 // ascending order and the first kEstThreads threads form the sums in a fixed
 // order, so every caller (the per-stage kernel, the fused step in either
 // form) gets the same float.
+//
+// That is the general path; most rows need neither radix select.  theta1 may be any lower bound that
+// at least k maxima reach and not many more do: est_binned counts the maxima
+// in 2048 linear bins below the row's maximum (one LDS pass), takes the edge
+// of the bin in which the k-th lies, re-reads the 16 logits of each maximum
+// at or above it, lists the tokens at or above the edge, and finds the k-th
+// largest of those few hundred by counting ranks.  Rows that do not suit the
+// bins (fewer than k maxima within 64 doublings of the top, more than 1024 at
+// the edge, NaN or infinite logits) take the general path.
 #pragma once
 
 #include "entropy_dev.h"
@@ -53,10 +62,10 @@ static_assert(kEstRankMax <= kEstBins, "candidates reuse the histogram");
 struct EstShared {
   alignas(16) unsigned hist[kEstBins];   // radix histogram, then candidates or run offsets
   unsigned red[2 * kEstMaxWaves];
-  float fred[2 * kEstWaves];
+  float fred[2 * kEstMaxWaves];
   int ired[kEstMaxWaves];
   float M, S;
-  int digit, krem, nq, ncand, rgt;
+  int digit, krem, nq, ncand, rgt, odd;
   unsigned rv;
 };
 
@@ -329,6 +338,241 @@ __device__ __forceinline__ int est_qualifying(const Src& src, int n1, unsigned t
   return nq;
 }
 
+// The estimate from the top-k multiset's sums: s, w over the values above the
+// k-th largest (key theta, n_gt of them above it), M, S the row's maximum and
+// mass.
+__device__ __forceinline__ float est_entropy(int est, int k, int V, unsigned theta, int n_gt, float s,
+                                             float w, float M, float S) {
+#pragma clang fp contract(off)
+  const float dt = est_key_value(theta) - M;
+  const float et = __builtin_amdgcn_exp2f(dt);
+  const float nt = static_cast<float>(k - n_gt);
+  const float SK = s + nt * et;
+  const float WK = w + ((et > 0.f) ? nt * (et * dt) : 0.f);
+  const float Ht = (log2f(SK) - WK / SK) * kLn2;
+  if (est != ENT_EST_TAIL) return Ht;
+  float mbar = (S - SK) / S;
+  mbar = fminf(fmaxf(mbar, 0.f), 1.f);
+  const float hb = (mbar > 0.f && mbar < 1.f) ? -mbar * logf(mbar) - (1.f - mbar) * log1pf(-mbar)
+                                              : 0.f;
+  return Ht + hb + mbar * logf(static_cast<float>(V - k));
+}
+
+// The binned form of row_estimate (see the top of this file), by kBinThreads
+// threads, every one of which must call it.  True: *H is the estimate (in
+// every thread); false: the row needs the general path, whose LDS it left
+// free.  It is latency: one pass over the maxima, one round trip for the
+// re-read logits, ten barriers.  On the 8B step (64 rows of 128256 logits,
+// k = 256) the launch with the estimate takes 25 us against 36 with the radix
+// selects, the step 244.6 against 255.5.
+constexpr int kBinThreads = 512;
+constexpr int kBinMaxima4 = 8;        // float4 of maxima per thread, at most (vocab <= 262144)
+constexpr int kBinCap = 1024;         // maxima at the edge, and tokens listed, at most
+static_assert(ENT_EST_MAX_K <= kBinCap / 2, "room above the k-th maximum");
+constexpr float kBinsPerUnit = 32.f;  // bins per doubling
+__device__ __forceinline__ float est_bin_pos(float v, float M) {   // monotone in v; M: 2048
+  return (v - M) * kBinsPerUnit + static_cast<float>(kEstBins);
+}
+
+// Exclusive offset of this thread's n among the workgroup's, in thread order,
+// and the total (one barrier; sh.ired is free again after another).
+__device__ __forceinline__ int est_block_offset(int n, EstShared& sh, int& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int incl = static_cast<int>(wave_scan_u(static_cast<unsigned>(n)));
+  if (lane == 63) sh.ired[wave] = incl;
+  __syncthreads();
+  int off = incl - n;
+  total = 0;
+#pragma unroll
+  for (int w = 0; w < kBinThreads / 64; ++w) {
+    if (w < wave) off += sh.ired[w];
+    total += sh.ired[w];
+  }
+  return off;
+}
+
+__device__ __forceinline__ bool est_binned(int est, int k, const float* __restrict__ tm, int n1,
+                                           const float* __restrict__ row, int V, float c2, int slots,
+                                           unsigned* lds, EstShared& sh, float* H) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  float4 v[kBinMaxima4];
+#pragma unroll
+  for (int u = 0; u < kBinMaxima4; ++u) {
+    const int i4 = t + u * kBinThreads;
+    v[u] = i4 < n1 / 4 ? reinterpret_cast<const float4*>(tm)[i4]
+                       : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+  }
+  for (int i = t; i < kEstBins; i += kBinThreads) sh.hist[i] = 0u;
+  if (t == 0) sh.digit = -1;
+  __syncthreads();                         // the bins are clear; M and S of wave 0 are there
+  const float M = sh.M, S = sh.S;
+  if (sh.odd) return false;
+#pragma unroll
+  for (int u = 0; u < kBinMaxima4; ++u) {
+    if (u * kBinThreads >= n1 / 4) break;
+    const float e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const float x = est_bin_pos(e[c], M);
+      if (x >= 0.f) atomicAdd(&sh.hist[min(static_cast<int>(x), kEstBins - 1)], 1u);
+    }
+  }
+  __syncthreads();
+  if (wave == 0) {
+    // Lane l holds bins BPL l .. BPL l + BPL - 1: the bin of the k-th largest
+    // by suffix sums over the lanes.
+    constexpr int BPL = kEstBins / 64;
+    unsigned c[BPL], cl = 0;
+#pragma unroll
+    for (int j = 0; j < BPL; j += 4) {
+      const uint4 h = *reinterpret_cast<const uint4*>(&sh.hist[BPL * lane + j]);
+      c[j] = h.x;
+      c[j + 1] = h.y;
+      c[j + 2] = h.z;
+      c[j + 3] = h.w;
+      cl += h.x + h.y + h.z + h.w;
+    }
+    const unsigned incl = wave_scan_u(cl);
+    const unsigned suf = lane_at(static_cast<int>(incl), 63) - incl + cl;
+    const unsigned above = suf - cl, kk = static_cast<unsigned>(k);
+    if (above < kk && suf >= kk) {
+      unsigned run = above;
+#pragma unroll
+      for (int j = BPL - 1; j >= 0; --j)
+        if (run < kk) {
+          run += c[j];
+          if (run >= kk) sh.digit = BPL * lane + j;
+        }
+      sh.nq = static_cast<int>(run);       // maxima at or above that bin
+    }
+  }
+  __syncthreads();
+  const int edge = sh.digit, nq = sh.nq;
+  const int cap = min(slots / 2, kBinCap);
+  if (edge < 0 || nq > cap) {
+    __syncthreads();                       // both read before they are written again
+    return false;
+  }
+  // x < 2048 at bins below the top one: x >= edge is the test for all of them.
+  const float fe = static_cast<float>(edge);
+  unsigned* val = lds;
+  int* qual = reinterpret_cast<int*>(lds + slots / 2);
+  int n = 0, total;
+#pragma unroll
+  for (int u = 0; u < kBinMaxima4; ++u) {
+    n += est_bin_pos(v[u].x, M) >= fe;
+    n += est_bin_pos(v[u].y, M) >= fe;
+    n += est_bin_pos(v[u].z, M) >= fe;
+    n += est_bin_pos(v[u].w, M) >= fe;
+  }
+  int o = est_block_offset(n, sh, total);
+#pragma unroll
+  for (int u = 0; u < kBinMaxima4; ++u) {
+    const float e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (est_bin_pos(e[c], M) >= fe) qual[o++] = 4 * (t + u * kBinThreads) + c;
+  }
+  __syncthreads();
+  // The qualifying threads' logits, four of the 16 at a time, with the chunk
+  // pass's mapping and scaling; all of a thread's loads are issued together.
+  constexpr int kItems = 4 * kBinCap / kBinThreads;
+  float z[kItems][4];
+#pragma unroll
+  for (int u = 0; u < kItems; ++u) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) z[u][c] = -INFINITY;
+    const int it = t + u * kBinThreads;
+    if (u * kBinThreads < 4 * nq && it < 4 * nq) {
+      const int j = qual[it >> 2];
+      const int pos = (j / kEstChunkThreads) * kRowChunk + (j % kEstChunkThreads) * 4 +
+                      (it & 3) * kEstChunkThreads * 4;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const float x = row[min(pos + c, V - 1)];
+        z[u][c] = pos + c < V ? x : -INFINITY;
+      }
+    }
+  }
+  n = 0;
+#pragma unroll
+  for (int u = 0; u < kItems; ++u) {
+    if (u * kBinThreads >= 4 * nq) break;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      z[u][c] *= c2;
+      n += est_bin_pos(z[u][c], M) >= fe;
+    }
+  }
+  o = est_block_offset(n, sh, total);
+  const int a = total;                     // tokens at or above the edge: at least nq >= k
+  if (a > cap) {
+    __syncthreads();
+    return false;
+  }
+#pragma unroll
+  for (int u = 0; u < kItems; ++u) {
+    if (u * kBinThreads >= 4 * nq) break;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (est_bin_pos(z[u][c], M) >= fe) val[o++] = est_key(z[u][c]);
+  }
+  if (t < 4 && a + t < ((a + 3) & ~3)) val[a + t] = 0u;     // below every key
+  __syncthreads();
+  // Each listed token counts those above it; the k-th largest is the least
+  // token with fewer than k above it.
+  unsigned mine[kBinCap / kBinThreads], least = 0xFFFFFFFFu;
+  int gt[kBinCap / kBinThreads];
+#pragma unroll
+  for (int u = 0; u < kBinCap / kBinThreads; ++u) {
+    const int i = t + u * kBinThreads;
+    mine[u] = i < a ? val[i] : 0u;
+    gt[u] = k;
+    if (64 * wave + u * kBinThreads >= a) continue;         // uniform in the wave
+    int n = 0;
+#pragma unroll 8
+    for (int j = 0; j < (a + 3) / 4; ++j) {
+      const uint4 x = reinterpret_cast<const uint4*>(val)[j];
+      n += (x.x > mine[u]) + (x.y > mine[u]) + (x.z > mine[u]) + (x.w > mine[u]);
+    }
+    gt[u] = i < a ? n : k;
+    if (gt[u] < k) least = min(least, mine[u]);
+  }
+  least = wave_min_u(least);
+  if (lane == 0) sh.red[wave] = least;
+  __syncthreads();
+  unsigned theta = sh.red[0];
+#pragma unroll
+  for (int i = 1; i < kBinThreads / 64; ++i) theta = min(theta, sh.red[i]);
+#pragma unroll
+  for (int u = 0; u < kBinCap / kBinThreads; ++u)
+    if (gt[u] < k && mine[u] == theta) sh.rgt = gt[u];      // the same number from each
+  float s = 0.f, w = 0.f;
+#pragma unroll
+  for (int u = 0; u < kBinCap / kBinThreads; ++u)
+    if (mine[u] > theta) {
+      const float d = est_key_value(mine[u]) - M;
+      const float e = __builtin_amdgcn_exp2f(d);
+      s += e;
+      w += (e > 0.f) ? e * d : 0.f;
+    }
+  s = wave_sum(s);
+  w = wave_sum(w);
+  if (lane == 0) {
+    sh.fred[wave] = s;
+    sh.fred[kEstMaxWaves + wave] = w;
+  }
+  __syncthreads();
+  s = w = 0.f;
+#pragma unroll
+  for (int i = 0; i < kBinThreads / 64; ++i) {
+    s += sh.fred[i];
+    w += sh.fred[kEstMaxWaves + i];
+  }
+  *H = est_entropy(est, k, V, theta, sh.rgt, s, w, M, S);
+  return true;
+}
+
 // Estimate of row b: ENT_EST_TOPK gives H~, ENT_EST_TAIL gives H^ (k < |V|;
 // the caller takes the exact entropy when k >= |V|).  part: the chunk
 // triples; tmax: the chunk threads' maxima [B, C, 256]; T: the row's
@@ -357,14 +601,27 @@ __device__ __forceinline__ float row_estimate(int est, int k, const float* __res
     for (int i = lane; i < C; i += 64) mloc = fmaxf(mloc, pr[3 * i]);
     const float MG = wave_max(mloc);
     float s = 0.f;
+    bool odd = !(fabsf(MG) < INFINITY);
     for (int i = lane; i < C; i += 64) {
       const float sc = pr[3 * i + 1];
       if (sc > 0.f) s += sc * exp2f(pr[3 * i] - MG);
+      odd |= !(sc < INFINITY);             // a NaN or infinite logit in the chunk
     }
     s = wave_sum(s);
+    const bool any_odd = __any(odd);
     if (lane == 0) {
       sh.M = MG;
       sh.S = s;
+      sh.odd = any_odd;
+    }
+  }
+
+  const float c2 = __fdiv_rn(kLog2e, T);
+  if (NT == kBinThreads && k <= n1 && n1 <= 4 * kBinMaxima4 * kBinThreads) {
+    float H;
+    if (est_binned(est, k, tm, n1, row, V, c2, est_key_slots(C, k), lds, sh, &H)) {
+      __syncthreads();                     // the LDS is the caller's again
+      return H;
     }
   }
 
@@ -402,7 +659,6 @@ __device__ __forceinline__ float row_estimate(int est, int k, const float* __res
 
   // Stage 2: re-read the qualifying threads' logits (the chunk pass's
   // element mapping and scaling), 16 values each.
-  const float c2 = __fdiv_rn(kLog2e, T);
   for (int q = t; q < nq; q += NT) {
     const int j = qual[q];
     const int base = (j / kEstChunkThreads) * kRowChunk + (j % kEstChunkThreads) * 4;
@@ -444,25 +700,9 @@ __device__ __forceinline__ float row_estimate(int est, int k, const float* __res
     }
   s = est_block_sum(s, sh, 0);
   w = est_block_sum(w, sh, 1);
-  {
-#pragma clang fp contract(off)
-    const float dt = est_key_value(theta) - M;
-    const float et = __builtin_amdgcn_exp2f(dt);
-    const float nt = static_cast<float>(k - n_gt);
-    const float SK = s + nt * et;
-    const float WK = w + ((et > 0.f) ? nt * (et * dt) : 0.f);
-    const float Ht = (log2f(SK) - WK / SK) * kLn2;
-    float H = Ht;
-    if (est == ENT_EST_TAIL) {
-      float mbar = (S - SK) / S;
-      mbar = fminf(fmaxf(mbar, 0.f), 1.f);
-      const float hb = (mbar > 0.f && mbar < 1.f) ? -mbar * logf(mbar) - (1.f - mbar) * log1pf(-mbar)
-                                                  : 0.f;
-      H = Ht + hb + mbar * logf(static_cast<float>(V - k));
-    }
-    __syncthreads();
-    return H;
-  }
+  const float H = est_entropy(est, k, V, theta, n_gt, s, w, M, S);
+  __syncthreads();
+  return H;
 }
 
 }  // namespace

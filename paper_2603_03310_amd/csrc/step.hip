@@ -103,14 +103,14 @@ __global__ __launch_bounds__(kFoldThreads) void step_b1_kernel(
                                s_ps, sL);
   } else {
     seq = blockIdx.x;
+    const ControlState cs = controller_load(seq, h_prev, tau, temp);
     if (est != ENT_EST_EXACT) {
-      const float T = temp[seq];
-      const float H = row_estimate(est, est_k, part, tmax, sa.logits, sa.ld, sa.V, C, T * sa.t_cal,
+      const float H = row_estimate(est, est_k, part, tmax, sa.logits, sa.ld, sa.V, C, cs.T * sa.t_cal,
                                    seq, dyn_lds, esh);
-      if (threadIdx.x == 0) controller_update(seq, H, T, h_prev, tau, temp, h_out, nullptr, ct);
+      if (threadIdx.x == 0) controller_update(seq, H, cs, h_prev, tau, temp, h_out, nullptr, ct);
     } else if (threadIdx.x < 64) {
       const float H = row_entropy(part, C, seq);
-      if (threadIdx.x == 0) controller_update(seq, H, temp[seq], h_prev, tau, temp, h_out, nullptr, ct);
+      if (threadIdx.x == 0) controller_update(seq, H, cs, h_prev, tau, temp, h_out, nullptr, ct);
     }
     if constexpr (TICK)
       if (threadIdx.x == 0) __hip_atomic_store(h_out + seq, h_out[seq], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -123,9 +123,9 @@ __global__ __launch_bounds__(kFoldThreads) void step_b1_kernel(
 // Per sequence, block tables that fit the one-launch selection: the
 // selection's loads are issued first, then the first wave computes the row's
 // entropy and the controller update while they are in flight (with an
-// estimator, the estimate comes first), then the whole kept-block selection;
-// workgroups B .. 2B-1 sample.
-template <int F4, bool VEC>
+// estimator (EST), the estimate comes first), then the whole kept-block
+// selection; workgroups B .. 2B-1 sample.
+template <int F4, bool VEC, bool EST>
 __global__ __launch_bounds__(kSelThreads) void step_b_kernel(
     int B, const float* __restrict__ part, int C, float* temp, float* h_prev, float* tau,
     float* h_out, Control ct, const float* __restrict__ zbuf, const float* __restrict__ lse_part,
@@ -136,7 +136,6 @@ __global__ __launch_bounds__(kSelThreads) void step_b_kernel(
   static_assert(kSelThreads >= kSampleThreads && kSelThreads >= kEstThreads, "workgroup size");
   extern __shared__ __attribute__((aligned(16))) unsigned keys[];   // [MAXB] keys, [MAXB] blocks, estimator
   __shared__ SelectShared sh;
-  __shared__ EstShared esh;
   __shared__ SampleShared ssh;
   __shared__ float s_H;
   const int b = blockIdx.x;
@@ -145,19 +144,20 @@ __global__ __launch_bounds__(kSelThreads) void step_b_kernel(
     return;
   }
   SelectRegs<F4> R;
-  if (est != ENT_EST_EXACT) {
+  const ControlState cs = controller_load(b, h_prev, tau, temp);
+  if constexpr (EST) {
+    __shared__ EstShared esh;
     // The estimate needs most registers itself: the selection's loads follow it.
-    const float T = temp[b];
-    const float H = row_estimate(est, est_k, part, tmax, sa.logits, sa.ld, sa.V, C, T * sa.t_cal, b,
-                                 keys + est_lds_offset(2 * MAXB), esh);
-    if (threadIdx.x == 0) s_H = controller_update(b, H, T, h_prev, tau, temp, h_out, nullptr, ct);
+    const float H = row_estimate(est, est_k, part, tmax, sa.logits, sa.ld, sa.V, C, cs.T * sa.t_cal,
+                                 b, keys + est_lds_offset(2 * MAXB), esh);
+    if (threadIdx.x == 0) s_H = controller_update(b, H, cs, h_prev, tau, temp, h_out, nullptr, ct);
     select_load<F4>(zbuf, lse_part, tables, MAXB, nch_max, b, Hq, R);
   } else {
     select_load<F4>(zbuf, lse_part, tables, MAXB, nch_max, b, Hq, R);
     if (threadIdx.x < 64) {
       const float H = row_entropy(part, C, b);
       if (threadIdx.x == 0)
-        s_H = controller_update(b, H, temp[b], h_prev, tau, temp, h_out, nullptr, ct);
+        s_H = controller_update(b, H, cs, h_prev, tau, temp, h_out, nullptr, ct);
     }
   }
   const int N = ctx_lens[b];
@@ -258,7 +258,7 @@ hipError_t launch_decode_step(const ent_ctx* c, int B, const float* logits, long
     const size_t lds =
         static_cast<size_t>(est_lds_offset(2 * cf.max_blocks_per_seq)) * sizeof(unsigned) + est_lds;
 #define ENT_STEPB_CASE(FF, VV)                                                                   \
-  hipLaunchKernelGGL((step_b_kernel<FF, VV>), dim3(2 * B), dim3(kSelThreads), lds, s, B,        \
+  hipLaunchKernelGGL((est ? step_b_kernel<FF, VV, true> : step_b_kernel<FF, VV, false>), dim3(2 * B), dim3(kSelThreads), lds, s, B,        \
                      c->ent_part, c->chunks, st.temp, st.h_prev, st.tau, h_out, ct, c->zbuf,     \
                      c->lse_part, ctx_lens, tables, scores, theta, kept, c->kept_phys, n_kept,   \
                      cf.max_blocks_per_seq, cf.num_pool_blocks, c->lse_chunks, cf.num_q_heads,  \
