@@ -198,9 +198,8 @@ template <int D>
 hipError_t launch_score_valu_d(const ent_ctx* c, int B, const float* q, const float* ksum,
                                const int* tables, const int* ctx_lens, hipStream_t s) {
   const ent_config& cf = c->cfg;
-  const int Hq = cf.num_q_heads;
   const dim3 grid((cf.max_blocks_per_seq + kValuChunk - 1) / kValuChunk, B);
-  const size_t lds = (static_cast<size_t>(Hq) * D + static_cast<size_t>(kValuChunk) * Hq) * sizeof(float);
+  const size_t lds = score_valu_lds(cf.num_q_heads, D);
 #define ENT_SCORE_CASE(GG)                                                                    \
   case GG:                                                                                    \
     hipLaunchKernelGGL((score_valu_kernel<D, GG>), grid, dim3(kScoreThreads), lds, s, q,      \

@@ -253,6 +253,14 @@ __device__ __forceinline__ float reduce_heads(float (&a)[G], int li) {
   }
 }
 
+// LDS of the VALU scoring: the queries and a tile's block logits; up to
+// kFusedValuLds (four workgroups per CU, as many as the bf16 prologue has) it
+// shares a launch with the entropy pass.
+inline size_t score_valu_lds(int Hq, int D) {
+  return (static_cast<size_t>(Hq) * D + static_cast<size_t>(kValuChunk) * Hq) * sizeof(float);
+}
+constexpr size_t kFusedValuLds = 40 * 1024;
+
 // smem: q [Hq][D] fp32, then z tile [kValuChunk][Hq].
 template <int D, int G>
 __device__ __forceinline__ void score_valu_body(

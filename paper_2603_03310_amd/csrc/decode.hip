@@ -32,7 +32,7 @@
 //     B = P^T taken straight from the S^T accumulator registers, split into
 //         a bf16 high part and a bf16 remainder (two MFMAs), so P keeps
 //         about 16 bits.
-// fp32 path (VALU): the same decomposition with scalar dot products.
+// fp32 path (VALU): the same decomposition, a quarter dot product per lane.
 
 #include "blocks_dev.h"
 #include "entropy_dev.h"
@@ -145,9 +145,11 @@ __device__ __forceinline__ int wave_of(int x, int U, int W) {
 // use holds a unit.  With all ranges in use those steps took 50.7, 38.9 and
 // 61.6 us, most of it in the merge.
 constexpr int kMinUnits = 8, kTwoUnits = 32;
-__device__ __forceinline__ int ranges_used(int U, int R) {
+__host__ __device__ __forceinline__ int ranges_used(int U, int R) {
   const int half = (R + 1) / 2;
-  return max(1, min(U < half * kTwoUnits ? half : R, (U + kMinUnits - 1) / kMinUnits));
+  const int cap = U < half * kTwoUnits ? half : R, need = (U + kMinUnits - 1) / kMinUnits;
+  const int n = cap < need ? cap : need;
+  return n < 1 ? 1 : n;
 }
 
 // The bf16 decode's ranges, weighted by XCD: workgroups are dealt to the
@@ -613,9 +615,18 @@ __global__ __launch_bounds__(kThreads, 3) void decode_bf16_kernel(DecodeArgs a) 
   if (threadIdx.x == 0) a.rec[wg] = make_int2(owner, owner_last);
 }
 
-template <int D>
+// fp32: lane (t16, dq) holds dims dq D / 4 .. of token t16's key (16-byte
+// loads), so a score is a quarter dot product per lane and two adds across
+// lanes, every lane ends with its token's score and forms one weight per head;
+// the values of dims lane, lane + 64, ... take the 16 weights by readlane.
+// The next unit's tiles load behind the current one's arithmetic.  With one
+// lane per whole dot product (48 lanes idle at G = 1), every weight formed in
+// every lane and no prefetch the launch took 8.5 us at the fp32 tiny step, so
+// 5.5; with the scoring in the entropy pass's launch the step 30.6 -> 23.2.
+template <int D, int G>
 __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
-  constexpr int DPL = D / 64;     // dims per lane
+  constexpr int DPL = D / 64;     // dims per lane of the outputs
+  constexpr int KQ = D / 16;      // float4 of a quarter key row
   extern __shared__ int s_mem[];
   __shared__ int s_red[kWaves];
   int* s_pref = s_mem;
@@ -633,8 +644,7 @@ __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
   if (U == 0 || w >= W) return;
   const int u0 = range_begin(w, U, W), u1 = range_begin(w + 1, U, W);
   if (u0 >= u1) return;
-  const int t16 = lane & 15, hs = lane >> 4;
-  const int G = a.G;
+  const int t16 = lane & 15, dq = lane >> 4;
   const int Hq = a.Hkv * G;
   const float* q = static_cast<const float*>(a.q);
   const float* kc = static_cast<const float*>(a.kc);
@@ -642,9 +652,24 @@ __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
 
   int ubase = u0;
   UnitMeta win = unit_meta(a, ubase + lane, u1, s_pref, s_nk, s_N);
+  f32x4_t kt[KQ], vt[DPL][4], kn[KQ], vn[DPL][4];
+  auto load_tiles = [&](int i, f32x4_t (&kr)[KQ], f32x4_t (&vr)[DPL][4]) {
+    const int g = max(lane_at(win.seg, i), 0) % a.Hkv;
+    const long long tile =
+        (static_cast<long long>(max(lane_at(win.p, i), 0)) * a.Hkv + g) * kBlock * D;
+#pragma unroll
+    for (int x = 0; x < KQ; ++x)
+      kr[x] = *reinterpret_cast<const f32x4_t*>(kc + tile + t16 * D + dq * (D / 4) + 4 * x);
+#pragma unroll
+    for (int y = 0; y < DPL; ++y)
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+        vr[y][x] = *reinterpret_cast<const f32x4_t*>(vc + tile + (lane + 64 * y) * kBlock + 4 * x);
+  };
+  load_tiles(0, kt, vt);
   int cur_seg = -1;
-  long long qbase = 0;
-  float m_run[kMaxGroup], l_run[kMaxGroup], o[kMaxGroup][DPL];
+  const float* qrow = q;                // this lane's quarter of the segment's queries
+  float m_run[G], l_run[G], o[G][DPL];
 
   auto flush = [&]() {
     const int b = cur_seg / a.Hkv, g = cur_seg % a.Hkv;
@@ -652,9 +677,10 @@ __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
     const int seg_end = seg_start + s_nk[b];
     const bool whole = seg_start >= u0 && seg_end <= u1;
     const long long slot = static_cast<long long>(w) + cur_seg;
+    if (!whole && lane == 0 && seg_start >= u0)
+      a.rec[w] = make_int2(cur_seg, wave_of(seg_end - 1, U, W));
 #pragma unroll
-    for (int h = 0; h < kMaxGroup; ++h) {
-      if (h >= G) continue;
+    for (int h = 0; h < G; ++h) {
       if (whole) {
         const long long oh = static_cast<long long>(b) * Hq + g * G + h;
         const float inv = l_run[h] > 0.f ? 1.f / l_run[h] : 0.f;
@@ -663,8 +689,6 @@ __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
         if (lane == 0 && a.lse)
           a.lse[oh] = l_run[h] > 0.f ? (m_run[h] + log2f(l_run[h])) * kLn2 : -INFINITY;
       } else {
-        if (h == 0 && lane == 0 && seg_start >= u0)
-          a.rec[w] = make_int2(cur_seg, wave_of(seg_end - 1, U, W));
 #pragma unroll
         for (int y = 0; y < DPL; ++y) a.part_acc[(slot * G + h) * D + lane + 64 * y] = o[h][y];
         if (lane == 0) {
@@ -681,72 +705,69 @@ __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
       ubase = u;
       i = 0;
       win = unit_meta(a, ubase + lane, u1, s_pref, s_nk, s_N);
+      load_tiles(0, kt, vt);
     }
     const int seg = lane_at(win.seg, i);
     if (seg != cur_seg) {
       if (cur_seg >= 0) flush();
       cur_seg = seg;
       const int b = seg / a.Hkv, g = seg % a.Hkv;
-      qbase = (static_cast<long long>(b) * Hq + g * G) * D;
+      qrow = q + (static_cast<long long>(b) * Hq + g * G) * D + dq * (D / 4);
 #pragma unroll
-      for (int h = 0; h < kMaxGroup; ++h) {
+      for (int h = 0; h < G; ++h) {
         m_run[h] = -INFINITY;
         l_run[h] = 0.f;
 #pragma unroll
         for (int y = 0; y < DPL; ++y) o[h][y] = 0.f;
       }
     }
+    // Past the window or the range the current tiles are read again, and dropped.
+    load_tiles((i + 1 < kWindow && u + 1 < u1) ? i + 1 : i, kn, vn);
     const int p = lane_at(win.p, i);
     const int nv = lane_at(win.nv, i);
-    if (p < 0) continue;
-    const long long tile = (static_cast<long long>(p) * a.Hkv + (seg % a.Hkv)) * kBlock * D;
-    // Scores: lane (t16, hs) takes token t16 for heads hs, hs+4, hs+8, hs+12.
-    float sc[4];
+    if (p >= 0) {
+      if (nv < kBlock) {
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      const int h = hs + 4 * x;
-      float dot = 0.f;
-      if (h < G && t16 < nv) {
-        for (int d = 0; d < D; ++d) dot += q[qbase + h * D + d] * kc[tile + t16 * D + d];
-        sc[x] = dot * a.scale_log2;
-      } else {
-        sc[x] = -INFINITY;
+        for (int y = 0; y < DPL; ++y)
+#pragma unroll
+          for (int tt = 0; tt < kBlock; ++tt)
+            if (tt >= nv) vt[y][tt / 4][tt % 4] = 0.f;
+      }
+#pragma unroll
+      for (int h = 0; h < G; ++h) {
+        float dot = 0.f;
+#pragma unroll
+        for (int x = 0; x < KQ; ++x) {
+          const f32x4_t qv = *reinterpret_cast<const f32x4_t*>(qrow + h * D + 4 * x);
+          dot += qv[0] * kt[x][0] + qv[1] * kt[x][1] + qv[2] * kt[x][2] + qv[3] * kt[x][3];
+        }
+        dot = xor_add<32>(xor_add<16>(dot));
+        const float sc = t16 < nv ? dot * a.scale_log2 : -INFINITY;
+        const float mb = xor_max<8>(xor_max<4>(xor_max<2>(xor_max<1>(sc))));
+        const float m_new = fmaxf(m_run[h], mb);
+        const float alpha = exp2f(m_run[h] - m_new);
+        const float pt = exp2f(sc - m_new);
+        l_run[h] = l_run[h] * alpha + xor_add<8>(xor_add<4>(xor_add<2>(xor_add<1>(pt))));
+        m_run[h] = m_new;
+        float acc[DPL];
+#pragma unroll
+        for (int y = 0; y < DPL; ++y) acc[y] = 0.f;
+#pragma unroll
+        for (int tt = 0; tt < kBlock; ++tt) {
+          const float pw = lane_at(pt, tt);
+#pragma unroll
+          for (int y = 0; y < DPL; ++y) acc[y] += pw * vt[y][tt / 4][tt % 4];
+        }
+#pragma unroll
+        for (int y = 0; y < DPL; ++y) o[h][y] = o[h][y] * alpha + acc[y];
       }
     }
-    float vv[DPL][kBlock];
+#pragma unroll
+    for (int x = 0; x < KQ; ++x) kt[x] = kn[x];
 #pragma unroll
     for (int y = 0; y < DPL; ++y)
 #pragma unroll
-      for (int tt = 0; tt < kBlock; ++tt)
-        vv[y][tt] = (tt < nv) ? vc[tile + (lane + 64 * y) * kBlock + tt] : 0.f;
-#pragma unroll
-    for (int h = 0; h < kMaxGroup; ++h) {
-      if (h >= G) continue;
-      float st[kBlock];
-      float mb = -INFINITY;
-#pragma unroll
-      for (int tt = 0; tt < kBlock; ++tt) {
-        st[tt] = lane_at(sc[h >> 2], 16 * (h & 3) + tt);
-        mb = fmaxf(mb, st[tt]);
-      }
-      const float m_new = fmaxf(m_run[h], mb);
-      const float alpha = exp2f(m_run[h] - m_new);
-      float lsum = 0.f;
-      float acc[DPL];
-#pragma unroll
-      for (int y = 0; y < DPL; ++y) acc[y] = 0.f;
-#pragma unroll
-      for (int tt = 0; tt < kBlock; ++tt) {
-        const float pt = exp2f(st[tt] - m_new);
-        lsum += pt;
-#pragma unroll
-        for (int y = 0; y < DPL; ++y) acc[y] += pt * vv[y][tt];
-      }
-      l_run[h] = l_run[h] * alpha + lsum;
-#pragma unroll
-      for (int y = 0; y < DPL; ++y) o[h][y] = o[h][y] * alpha + acc[y];
-      m_run[h] = m_new;
-    }
+      for (int x = 0; x < 4; ++x) vt[y][x] = vn[y][x];
   }
   flush();
 }
@@ -875,6 +896,18 @@ int occupancy_blocks(K kernel, size_t lds) {
   return n;
 }
 
+// The fp32 decode for a group size (1, 2, 4, 8 or 16).
+template <int D>
+void (*f32_kernel(int G))(DecodeArgs) {
+  switch (G) {
+    case 1: return decode_f32_kernel<D, 1>;
+    case 2: return decode_f32_kernel<D, 2>;
+    case 4: return decode_f32_kernel<D, 4>;
+    case 8: return decode_f32_kernel<D, 8>;
+    default: return decode_f32_kernel<D, 16>;
+  }
+}
+
 size_t plan_lds_bytes(int B) { return static_cast<size_t>(3 * B + 1) * sizeof(int); }
 
 // bf16 decode: the workgroup's cut partials, then the plan.
@@ -900,8 +933,7 @@ int decode_grid_size(const ent_ctx* c) {
     per_cu = cf.head_dim == 128 ? occupancy_blocks(decode_bf16_kernel<128>, lds16)
                                 : occupancy_blocks(decode_bf16_kernel<64>, lds16);
   else
-    per_cu = cf.head_dim == 128 ? occupancy_blocks(decode_f32_kernel<128>, lds)
-                                : occupancy_blocks(decode_f32_kernel<64>, lds);
+    per_cu = occupancy_blocks(cf.head_dim == 128 ? f32_kernel<128>(c->group) : f32_kernel<64>(c->group), lds);
   return c->num_cu * std::min(per_cu, kDecodePerCu);
 }
 
@@ -940,7 +972,12 @@ hipError_t launch_decode(const ent_ctx* c, int B, const void* q, const void* k_c
   a.R = cf.kv_dtype == ENT_BF16 ? c->decode_grid : a.W;
   a.scale_log2 = cf.scale * kLog2e;
   const size_t lds = plan_lds_bytes(B);
-  const dim3 grid(c->decode_grid);
+  // No more workgroups than the ranges that the batch's tables can fill.
+  const int umax = static_cast<int>(static_cast<long long>(B) * cf.max_blocks_per_seq * cf.num_kv_heads);
+  const int nwg = cf.kv_dtype == ENT_BF16
+                      ? ranges_used(umax, c->decode_grid)
+                      : std::min(c->decode_grid, umax / kWaves + 1);
+  const dim3 grid(nwg);
   if (cf.kv_dtype == ENT_BF16) {
     const size_t lds16 = decode_lds_bytes(B, c->group, cf.head_dim);
     if (cf.head_dim == 128)
@@ -948,16 +985,14 @@ hipError_t launch_decode(const ent_ctx* c, int B, const void* q, const void* k_c
     else
       hipLaunchKernelGGL(decode_bf16_kernel<64>, grid, dim3(kThreads), lds16, s, a);
   } else {
-    if (cf.head_dim == 128)
-      hipLaunchKernelGGL(decode_f32_kernel<128>, grid, dim3(kThreads), lds, s, a);
-    else
-      hipLaunchKernelGGL(decode_f32_kernel<64>, grid, dim3(kThreads), lds, s, a);
+    auto k = cf.head_dim == 128 ? f32_kernel<128>(c->group) : f32_kernel<64>(c->group);
+    hipLaunchKernelGGL(k, grid, dim3(kThreads), lds, s, a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // Slices per segment: four outputs per merge thread.
   a.nsl = (c->group * cf.head_dim / 4 + kThreads - 1) / kThreads;
-  const int n_combine = a.R * a.nsl;
+  const int n_combine = (cf.kv_dtype == ENT_BF16 ? nwg : nwg * kWaves) * a.nsl;
   if (ap || sp) {
     const int nS = sp ? B : 0;
     const dim3 g2(n_combine + (ap ? B : 0) + nS);

@@ -145,6 +145,11 @@ struct PrologueArgs {
   unsigned* flags;
 };
 hipError_t launch_prologue(const ent_ctx* c, const PrologueArgs& a, hipStream_t s);
+// fp32 queries: the entropy pass and the block scoring in one launch.  False
+// (nothing launched) where the scoring's LDS would cost the entropy workgroups
+// residency: launch_prologue and launch_score_valu then.
+bool launch_prologue_f32(const ent_ctx* c, const PrologueArgs& a, const float* q, hipStream_t s,
+                         hipError_t* e);
 int prologue_grid_size(const ent_ctx* c);
 // Residency of the fused step's tile launch with and without the selection
 // inside (ent_ctx::b1_occ_*).

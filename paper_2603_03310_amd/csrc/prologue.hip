@@ -223,6 +223,31 @@ __global__ __launch_bounds__(kProThreads) void prologue_kernel(PrologueArgs a) {
   }
 }
 
+// fp32 queries: the scoring tiles (VALU, score_valu_body) and the entropy
+// chunks as one dense grid.  Each pass is a chain of a few round trips; as two
+// launches (3.6 and 6.3 us at the fp32 tiny step) the second chain waited for
+// the first; together 6.2.
+template <bool VEC, int D, int G>
+__global__ __launch_bounds__(kProThreads) void prologue_f32_kernel(PrologueArgs a, const float* q) {
+  static_assert(kProThreads == kScoreThreads, "workgroup size");
+  extern __shared__ __attribute__((aligned(16))) float s_valu[];   // queries, block logits
+  __shared__ float red[16];
+  const int tiles = (a.MAXB + kValuChunk - 1) / kValuChunk;
+  const int nsc = a.B * tiles;
+  const int id = blockIdx.x;
+  if (id < nsc) {
+    const int b = id / tiles;
+    score_valu_body<D, G>(q, a.ksum, a.tables, a.ctx_lens, a.zbuf, a.lse_part, a.Hkv, a.MAXB, a.P,
+                          a.nch_max, a.scale, a.flags, id - b * tiles, b, s_valu);
+    return;
+  }
+  const int e = id - nsc;
+  const int b = e / a.C;
+  entropy_chunk_body<VEC>(a.logits, a.ld, a.V, a.C, a.temp, a.t_cal, a.part, a.row_stats, a.tmax,
+                          e - b * a.C, b, red);
+  if (e == b * a.C && threadIdx.x == 0 && a.temp_used) a.temp_used[b] = a.temp[b];
+}
+
 template <bool VEC, int D>
 int prologue_per_cu() {
   int n = 0;
@@ -271,6 +296,43 @@ hipError_t launch_prologue(const ent_ctx* c, const PrologueArgs& a, hipStream_t 
   }
 #undef ENT_PRO_LAUNCH
   return hipGetLastError();
+}
+
+bool launch_prologue_f32(const ent_ctx* c, const PrologueArgs& a, const float* q, hipStream_t s,
+                         hipError_t* e) {
+  const ent_config& cf = c->cfg;
+  const long long jobs =
+      static_cast<long long>(a.B) * ((cf.max_blocks_per_seq + kValuChunk - 1) / kValuChunk + a.C);
+  const size_t lds = score_valu_lds(cf.num_q_heads, cf.head_dim);
+  if (lds > kFusedValuLds || jobs >= (1ll << 31)) return false;
+  const bool vec = row_vec_ok(a.logits, a.ld);
+  const dim3 grid(static_cast<unsigned>(jobs));
+#define ENT_PRO_F32(DD, GG)                                                                          \
+  case GG:                                                                                           \
+    if (vec)                                                                                         \
+      hipLaunchKernelGGL((prologue_f32_kernel<true, DD, GG>), grid, dim3(kProThreads), lds, s, a, q);  \
+    else                                                                                             \
+      hipLaunchKernelGGL((prologue_f32_kernel<false, DD, GG>), grid, dim3(kProThreads), lds, s, a, q); \
+    break;
+#define ENT_PRO_F32_D(DD)                   \
+  switch (a.G) {                            \
+    ENT_PRO_F32(DD, 1)                      \
+    ENT_PRO_F32(DD, 2)                      \
+    ENT_PRO_F32(DD, 4)                      \
+    ENT_PRO_F32(DD, 8)                      \
+    ENT_PRO_F32(DD, 16)                     \
+    default:                                \
+      return false;                         \
+  }
+  if (cf.head_dim == 128) {
+    ENT_PRO_F32_D(128)
+  } else {
+    ENT_PRO_F32_D(64)
+  }
+#undef ENT_PRO_F32_D
+#undef ENT_PRO_F32
+  *e = hipGetLastError();
+  return true;
 }
 
 }  // namespace ent

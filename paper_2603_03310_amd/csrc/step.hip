@@ -5,8 +5,9 @@
 //
 //   A  block scoring and the entropy chunk passes in one persistent grid
 //      (prologue.hip): both stream from HBM (block summaries, logits) and
-//      do not depend on each other (fp32 queries: scoring is a second
-//      launch, on the VALU); each row's T_t is recorded in temp_used;
+//      do not depend on each other (fp32 queries: scoring on the VALU, in a
+//      launch of its own where its LDS is large); each row's T_t is recorded
+//      in temp_used;
 //   B  one workgroup per sequence: the row's entropy from the chunk triples,
 //      the controller update and the kept-block selection under the
 //      entropy-driven budget; in the same launch, on workgroups of their
@@ -233,12 +234,12 @@ hipError_t launch_decode_step(const ent_ctx* c, int B, const float* logits, long
   pa.nch_max = c->lse_chunks;
   pa.scale = cf.scale;
   pa.flags = c->dev_flags;
-  hipError_t e = launch_prologue(c, pa, s);
-  if (e != hipSuccess) return e;
-  if (!bf16) {
-    e = launch_score_valu(c, B, q, ksum, tables, ctx_lens, s);
-    if (e != hipSuccess) return e;
+  hipError_t e = hipSuccess;
+  if (bf16 || !launch_prologue_f32(c, pa, static_cast<const float*>(q), s, &e)) {
+    e = launch_prologue(c, pa, s);
+    if (e == hipSuccess && !bf16) e = launch_score_valu(c, B, q, ksum, tables, ctx_lens, s);
   }
+  if (e != hipSuccess) return e;
 
   SampleArgs sa;
   sa.logits = logits;
