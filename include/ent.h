@@ -279,8 +279,8 @@ int ent_sample(ent_ctx* c, int B, const float* logits, long long ld, const float
  * block scoring share one launch; the per-sequence entropy, controller and
  * selection share a second; decode attention follows, and sampling shares
  * the launch that merges the split attention segments.  In the exact
- * scoring mode the step is the four staged calls in order and ksum may be
- * NULL.
+ * scoring mode the scoring pass over the keys is a launch of its own and
+ * ksum may be NULL.
  * Arguments as in those calls: st is updated in place (tau, h_prev, temp
  * for the next step); h_out, temp_used, tokens: [B]; kept, n_kept, out as
  * in ent_sparse_paged_decode; row_stats, lse, scores, theta nullable.
@@ -309,8 +309,7 @@ int ent_kv_append(ent_ctx* c, int B, const void* k_new, const void* v_new,
  * ent_kv_append of this step's new token, bit-identical to the two calls in
  * that order.  k_new, v_new: [B, H_kv, d] (kv_dtype, 16-byte aligned).  The
  * append runs on workgroups of its own inside the step's last launch, the
- * merge of split attention segments, which reads nothing the append writes
- * (in the exact scoring mode: the staged calls, then the append).
+ * merge of split attention segments, which reads nothing the append writes.
  * Arguments as in the two calls: ctx_lens is incremented, k_cache, v_cache
  * and ksum receive the new token. */
 int ent_decode_step_append(ent_ctx* c, int B, const float* logits, long long ld, ent_state st,

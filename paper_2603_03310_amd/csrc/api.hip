@@ -389,21 +389,6 @@ int ent_decode_step(ent_ctx* c, int B, const float* logits, long long ld, ent_st
   if (!aligned(q, 16) || (!exact && !aligned(ksum, 16)) || !aligned(k_cache, 16) ||
       !aligned(v_cache, 16) || !aligned(out, 16))
     return fail(c, ENT_E_INVAL, "ent_decode_step: q, ksum, caches and out need 16-byte alignment");
-  if (exact) {
-    // The conservative scoring mode: the staged calls in order (every
-    // argument they check was checked above, so none fails part-way).  The
-    // sampler reuses the entropy pass's row statistics.
-    float* stats = row_stats ? row_stats : c->stats_tmp;
-    if (int r = ent_entropy_temperature(c, B, logits, ld, st, h_out, temp_used, stats, stream))
-      return r;
-    if (int r = ent_block_select(c, B, q, ksum, k_cache, block_tables, ctx_lens, h_out, kept,
-                                 n_kept, scores, theta, st.kappa, stream))
-      return r;
-    if (int r = ent_sparse_paged_decode(c, B, q, k_cache, v_cache, block_tables, ctx_lens, kept,
-                                        n_kept, out, lse, stream))
-      return r;
-    return ent_sample(c, B, logits, ld, stats, temp_used, uniforms, tokens, stream);
-  }
   const hipError_t e = ent::launch_decode_step(c, B, logits, ld, st, q, k_cache, v_cache, ksum,
                                                block_tables, ctx_lens, uniforms, h_out,
                                                temp_used, row_stats, kept, n_kept, out, lse,
@@ -428,25 +413,16 @@ int ent_decode_step_append(ent_ctx* c, int B, const float* logits, long long ld,
     return fail(c, ENT_E_INVAL, "ent_decode_step_append: NULL required pointer");
   if (!aligned(k_new, 16) || !aligned(v_new, 16))
     return fail(c, ENT_E_INVAL, "ent_decode_step_append: k_new and v_new need 16-byte alignment");
-  if (exact) {
-    // The staged step, then the append.
-    if (int r = ent_decode_step(c, B, logits, ld, st, q, k_cache, v_cache, ksum, block_tables,
-                                ctx_lens, uniforms, h_out, temp_used, row_stats, kept, n_kept, out,
-                                lse, tokens, scores, theta, stream))
-      return r;
-    return ent_kv_append(c, B, k_new, v_new, block_tables, ctx_lens, k_cache, v_cache, ksum,
-                         stream);
-  }
-  if (!logits || !st.h_prev || !st.tau || !st.temp || !q || !k_cache || !v_cache || !ksum ||
-      !block_tables || !ctx_lens || !uniforms || !h_out || !temp_used || !kept || !n_kept || !out ||
-      !tokens)
+  if (!logits || !st.h_prev || !st.tau || !st.temp || !q || !k_cache || !v_cache ||
+      (!exact && !ksum) || !block_tables || !ctx_lens || !uniforms || !h_out || !temp_used || !kept ||
+      !n_kept || !out || !tokens)
     return fail(c, ENT_E_INVAL, "ent_decode_step_append: NULL required pointer");
   if (ld < c->cfg.vocab) return fail(c, ENT_E_INVAL, "ent_decode_step_append: ld < vocab");
   if (h_out == st.h_prev) return fail(c, ENT_E_INVAL, "ent_decode_step_append: h_out aliases h_prev");
   if (temp_used == st.temp)
     return fail(c, ENT_E_INVAL, "ent_decode_step_append: temp_used aliases temp");
-  if (!aligned(q, 16) || !aligned(ksum, 16) || !aligned(k_cache, 16) || !aligned(v_cache, 16) ||
-      !aligned(out, 16))
+  if (!aligned(q, 16) || (!exact && !aligned(ksum, 16)) || !aligned(k_cache, 16) ||
+      !aligned(v_cache, 16) || !aligned(out, 16))
     return fail(c, ENT_E_INVAL,
                 "ent_decode_step_append: q, ksum, caches and out need 16-byte alignment");
   const ent::AppendArgs ap =

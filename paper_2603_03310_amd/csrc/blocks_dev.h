@@ -599,13 +599,43 @@ __device__ __forceinline__ void block_score_body(const float* __restrict__ zbuf,
   block_score_tile<kRowThreads, kTileBlocks>(zbuf, sL, scores, Hq, MAXB, b, N, nb, j0);
 }
 
+// Step B of the exact mode for blocks j0 .. j0 + TB - 1 of sequence b by NT
+// threads, from the pairs (log mass, mean logit) of every block and head: four
+// lanes per block (heads qq, qq + 4, ...).  COH as block_score_tile.
+template <int NT, int TB, bool COH = false>
+__device__ __forceinline__ void exact_score_tile(const float2* __restrict__ ex, const float* sL,
+                                                 float* __restrict__ scores, int Hq, int MAXB, int b,
+                                                 int nb, int j0) {
+  const int t = threadIdx.x, qq = t & 3;
+  for (int jp = j0; jp < j0 + TB; jp += NT / 4) {
+    const int j = jp + (t >> 2);
+    float acc = 0.f;
+    if (j < nb) {
+      const float2* er = ex + (static_cast<long long>(b) * MAXB + j) * Hq;
+#pragma unroll 8
+      for (int h = qq; h < Hq; h += 4) {
+        const float2 e = er[h];
+        acc += expf(e.x - sL[h]) * (sL[h] - e.y);
+      }
+    }
+    acc = xor_add<2>(xor_add<1>(acc));
+    if (j < nb && qq == 0) {
+      float* dst = scores + static_cast<long long>(b) * MAXB + j;
+      const float I = __fdiv_rn(acc, static_cast<float>(Hq));
+      if (COH) __hip_atomic_store(dst, I, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else *dst = I;
+    }
+  }
+}
+
 // Steps A and B together for blocks j0 .. j0 + kStepTileBlocks - 1 of
 // sequence b, by kFoldThreads threads (the fused step's long-table form):
 // L_h merged in LDS exactly as step A's own launch merges it, then the
-// tile's scores.  Every thread must call it.
+// tile's scores (EX: the exact mode's, from ex).  Every thread must call it.
 constexpr int kStepTileBlocks = 256;
-template <bool COH = false>
+template <bool COH, bool EX>
 __device__ __forceinline__ void lse_block_score_body(const float* __restrict__ zbuf,
+                                                     const float2* __restrict__ ex,
                                                      const float* __restrict__ lse_part,
                                                      const int* __restrict__ ctx_lens,
                                                      float* __restrict__ scores, int Hq, int MAXB,
@@ -617,7 +647,10 @@ __device__ __forceinline__ void lse_block_score_body(const float* __restrict__ z
   if (j0 >= nb) return;
   lse_merge_body(lse_part, ctx_lens, sL, Hq, MAXB, nch_max, b, s_pm, s_ps);
   __syncthreads();
-  block_score_tile<kFoldThreads, kStepTileBlocks, COH>(zbuf, sL, scores, Hq, MAXB, b, N, nb, j0);
+  if constexpr (EX)
+    exact_score_tile<kFoldThreads, kStepTileBlocks, COH>(ex, sL, scores, Hq, MAXB, b, nb, j0);
+  else
+    block_score_tile<kFoldThreads, kStepTileBlocks, COH>(zbuf, sL, scores, Hq, MAXB, b, N, nb, j0);
 }
 
 constexpr int kSelRankMax = 64;    // prefix groups this small are finished by counting ranks

@@ -277,17 +277,7 @@ __global__ __launch_bounds__(kRowThreads) void exact_block_score_kernel(
   if (j0 >= nb) return;
   for (int h = t; h < Hq; h += kRowThreads) sL[h] = L[static_cast<long long>(b) * Hq + h];
   __syncthreads();
-  const int j = j0 + (t >> 2), qq = t & 3;
-  float acc = 0.f;
-  if (j < nb) {
-    const float2* er = ex + (static_cast<long long>(b) * MAXB + j) * Hq;
-    for (int h = qq; h < Hq; h += 4) {
-      const float2 e = er[h];
-      acc += expf(e.x - sL[h]) * (sL[h] - e.y);
-    }
-  }
-  acc = xor_add<2>(xor_add<1>(acc));
-  if (j < nb && qq == 0) scores[static_cast<long long>(b) * MAXB + j] = __fdiv_rn(acc, static_cast<float>(Hq));
+  exact_score_tile<kRowThreads, kTileBlocks>(ex, sL, scores, Hq, MAXB, b, nb, j0);
 }
 
 }  // namespace

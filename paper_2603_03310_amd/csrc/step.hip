@@ -17,7 +17,10 @@
 //      of their own, L_h and the block scores per tile of 256 blocks, each
 //      sequence's selection on the last of its workgroups to finish (a
 //      ticket per sequence); sampling moves to D;
-//   C  kept-block decode attention;
+//      Exact token-level scoring: A is the entropy pass and then the scoring
+//      pass over every key, B always the tile launch (block scores from that
+//      pass's pairs): five launches, the 8B step 295.5 us, where the staged
+//      calls in order (nine launches) took 304.4;
 //   D  the merge of split decode segments (and, on workgroups of their own,
 //      ent_decode_step_append's append of the new token's K/V and, for long
 //      block tables, the sampling).
@@ -79,7 +82,7 @@ __device__ __forceinline__ void step_b1_select(int seq, const int* __restrict__ 
 // selection launch does.  Nothing waits for another workgroup.  Without,
 // the selection launch follows.  (Sampling runs in the merge launch of this
 // form.)
-template <bool VEC, bool TICK>
+template <bool VEC, bool TICK, bool EX>
 __global__ __launch_bounds__(kFoldThreads) void step_b1_kernel(
     int B, const float* __restrict__ part, int C, float* temp, float* h_prev, float* tau,
     float* h_out, Control ct, const float* __restrict__ zbuf, const float* __restrict__ lse_part,
@@ -87,7 +90,7 @@ __global__ __launch_bounds__(kFoldThreads) void step_b1_kernel(
     int ntile, SampleArgs sa, int est, int est_k, const float* __restrict__ tmax,
     const int* __restrict__ tables, float* __restrict__ theta, int* __restrict__ kept,
     int* __restrict__ kphys, int* __restrict__ n_kept, int P, Budget bu, unsigned* flags,
-    unsigned* tickets) {
+    unsigned* tickets, const float2* __restrict__ ex) {
   static_assert(kFoldThreads >= kEstThreads && kFoldThreads == kSelThreads, "workgroup size");
   // Estimator LDS, then (the selecting workgroup) the keys and encoded blocks.
   extern __shared__ __attribute__((aligned(16))) unsigned dyn_lds[];
@@ -100,8 +103,8 @@ __global__ __launch_bounds__(kFoldThreads) void step_b1_kernel(
     const int j0 = (r - seq * ntile) * kStepTileBlocks;
     const int N = ctx_lens[seq];
     if (N < 0 || N > MAXB * kBlock || j0 >= (N + kBlock - 1) / kBlock) return;   // no blocks
-    lse_block_score_body<TICK>(zbuf, lse_part, ctx_lens, scores, Hq, MAXB, nch_max, seq, j0, s_pm,
-                               s_ps, sL);
+    lse_block_score_body<TICK, EX>(zbuf, ex, lse_part, ctx_lens, scores, Hq, MAXB, nch_max, seq, j0,
+                                   s_pm, s_ps, sL);
   } else {
     seq = blockIdx.x;
     const ControlState cs = controller_load(seq, h_prev, tau, temp);
@@ -186,11 +189,14 @@ static size_t step_b1_lds(const ent_ctx* c, bool tickets) {
 void step_occupancy(ent_ctx* c) {
   c->b1_occ_plain = 0;
   c->b1_occ_ticket = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&c->b1_occ_plain, step_b1_kernel<true, false>,
-                                                   kFoldThreads, step_b1_lds(c, false)) != hipSuccess)
+  const bool ex = c->cfg.scoring == ENT_SCORE_EXACT;
+  auto plain = ex ? step_b1_kernel<true, false, true> : step_b1_kernel<true, false, false>;
+  auto ticket = ex ? step_b1_kernel<true, true, true> : step_b1_kernel<true, true, false>;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&c->b1_occ_plain, plain, kFoldThreads,
+                                                   step_b1_lds(c, false)) != hipSuccess)
     c->b1_occ_plain = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&c->b1_occ_ticket, step_b1_kernel<true, true>,
-                                                   kFoldThreads, step_b1_lds(c, true)) != hipSuccess)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&c->b1_occ_ticket, ticket, kFoldThreads,
+                                                   step_b1_lds(c, true)) != hipSuccess)
     c->b1_occ_ticket = 0;
 }
 
@@ -204,6 +210,7 @@ hipError_t launch_decode_step(const ent_ctx* c, int B, const float* logits, long
   const ent_config& cf = c->cfg;
   float* stats = row_stats ? row_stats : c->stats_tmp;
   const bool bf16 = cf.kv_dtype == ENT_BF16;
+  const bool exact = cf.scoring == ENT_SCORE_EXACT;
   PrologueArgs pa{};
   pa.B = B;
   pa.do_entropy = 1;
@@ -220,7 +227,7 @@ hipError_t launch_decode_step(const ent_ctx* c, int B, const float* logits, long
   const int est_mode = est ? cf.estimator : ENT_EST_EXACT;
   const size_t est_lds = est ? est_lds_bytes(c->chunks, cf.est_k) : 0;
   pa.tmax = est ? c->tmax : nullptr;
-  pa.do_score = bf16 ? 1 : 0;
+  pa.do_score = bf16 && !exact ? 1 : 0;
   pa.q = static_cast<const uint16_t*>(q);
   pa.ksum = ksum;
   pa.tables = tables;
@@ -235,7 +242,10 @@ hipError_t launch_decode_step(const ent_ctx* c, int B, const float* logits, long
   pa.scale = cf.scale;
   pa.flags = c->dev_flags;
   hipError_t e = hipSuccess;
-  if (bf16 || !launch_prologue_f32(c, pa, static_cast<const float*>(q), s, &e)) {
+  if (exact) {
+    e = launch_prologue(c, pa, s);
+    if (e == hipSuccess) e = launch_exact_scores(c, B, q, k_cache, tables, ctx_lens, s);
+  } else if (bf16 || !launch_prologue_f32(c, pa, static_cast<const float*>(q), s, &e)) {
     e = launch_prologue(c, pa, s);
     if (e == hipSuccess && !bf16) e = launch_score_valu(c, B, q, ksum, tables, ctx_lens, s);
   }
@@ -254,7 +264,7 @@ hipError_t launch_decode_step(const ent_ctx* c, int B, const float* logits, long
   const Control ct = make_control(cf);
   const Budget bu = make_budget(cf, st.kappa);
   const bool vec = row_vec_ok(logits, ld);
-  const int form = select_one_launch(cf.max_blocks_per_seq, cf.num_q_heads);
+  const int form = exact ? 0 : select_one_launch(cf.max_blocks_per_seq, cf.num_q_heads);
   if (form) {
     const size_t lds =
         static_cast<size_t>(est_lds_offset(2 * cf.max_blocks_per_seq)) * sizeof(unsigned) + est_lds;
@@ -293,13 +303,16 @@ hipError_t launch_decode_step(const ent_ctx* c, int B, const float* logits, long
     const bool tick = c->b1_occ_ticket >= c->b1_occ_plain &&
                       grid <= 2 * c->num_cu * c->b1_occ_plain;
     const size_t lds = tick ? step_b1_lds(c, true) : step_b1_lds(c, false);
-    auto k1 = tick ? (vec ? step_b1_kernel<true, true> : step_b1_kernel<false, true>)
-                   : (vec ? step_b1_kernel<true, false> : step_b1_kernel<false, false>);
+    auto k1 = tick ? (vec ? step_b1_kernel<true, true, false> : step_b1_kernel<false, true, false>)
+                   : (vec ? step_b1_kernel<true, false, false> : step_b1_kernel<false, false, false>);
+    if (exact)
+      k1 = tick ? (vec ? step_b1_kernel<true, true, true> : step_b1_kernel<false, true, true>)
+                : (vec ? step_b1_kernel<true, false, true> : step_b1_kernel<false, false, true>);
     hipLaunchKernelGGL(k1, dim3(grid), dim3(kFoldThreads), lds, s, B, c->ent_part,
                        c->chunks, st.temp, st.h_prev, st.tau, h_out, ct, c->zbuf, c->lse_part,
                        ctx_lens, sc, cf.num_q_heads, cf.max_blocks_per_seq, c->lse_chunks, ntile, sa,
                        est_mode, cf.est_k, c->tmax, tables, theta, kept, c->kept_phys, n_kept,
-                       cf.num_pool_blocks, bu, c->dev_flags, tick ? c->tickets : nullptr);
+                       cf.num_pool_blocks, bu, c->dev_flags, tick ? c->tickets : nullptr, c->exbuf);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (!tick) {
