@@ -1030,9 +1030,12 @@ __device__ __forceinline__ void select_load(const float* __restrict__ zbuf,
   }
 }
 
-template <int F4>
+// meanwhile() runs between the scores and the barrier after them (every thread
+// calls it), hval() gives the sequence's entropy after that barrier.
+template <int F4, class Meanwhile, class Entropy>
 __device__ __forceinline__ void select_finish(
-    const SelectRegs<F4>& R, int N, int nb, float hval, float* __restrict__ scores_out,
+    const SelectRegs<F4>& R, int N, int nb, Meanwhile meanwhile, Entropy hval,
+    float* __restrict__ scores_out,
     float* __restrict__ theta_out, int* __restrict__ kept, int* __restrict__ kphys,
     int* __restrict__ n_kept, int MAXB, int P, const Budget& bu, float kprev, int b, int Hq,
     unsigned* keys, int* tbl, SelectShared& sh) {
@@ -1093,9 +1096,10 @@ __device__ __forceinline__ void select_finish(
     const int j = t + i * kSelThreads;
     if (j < nb) tbl[j] = encode_phys(R.tb[i], j, nb, P);
   }
+  meanwhile();
   __syncthreads();
   float ku;
-  const int k = forced_budget(keep_budget(hval, nb, bu, kprev, &ku), nb, bu);
+  const int k = forced_budget(keep_budget(hval(), nb, bu, kprev, &ku), nb, bu);
   budget_record(bu, b, ku);       // every thread read kprev before the barriers above
   if (k <= 0) {
     select_none(theta_out, n_kept, b);
@@ -1119,8 +1123,8 @@ __device__ __forceinline__ void select_fused_body(
   int nb, k;
   if (!select_prepare(N, hval, theta_out, n_kept, MAXB, bu, kprev, flags, b, nb, k))
     return;
-  select_finish<F4>(R, N, nb, hval, scores_out, theta_out, kept, kphys, n_kept, MAXB, P, bu, kprev,
-                    b, Hq, keys, tbl, sh);
+  select_finish<F4>(R, N, nb, [] {}, [=] { return hval; }, scores_out, theta_out, kept, kphys, n_kept,
+                    MAXB, P, bu, kprev, b, Hq, keys, tbl, sh);
 }
 
 // Append of one token to sequence b's cache by one workgroup of

@@ -144,13 +144,21 @@ __device__ __forceinline__ void entropy_chunk_body(const float* __restrict__ log
 }
 
 // Entropy of row b from its C chunk triples, by one wave (result in every
-// lane).  A lane's first triple is loaded whole: up to 64 chunks (262144
-// logits) the merge is one memory round trip.
-__device__ __forceinline__ float row_entropy(const float* __restrict__ part, int C, int b) {
+// lane).  A lane's first triple is loaded whole, ahead if the caller likes:
+// up to 64 chunks (262144 logits) the merge then waits for memory once.
+struct RowTriple {
+  float m, s, w;
+};
+__device__ __forceinline__ RowTriple row_triple(const float* __restrict__ part, int C, int b) {
+  const int lane = threadIdx.x & 63;
+  const float* p = part + (static_cast<long long>(b) * C + min(lane, C - 1)) * 3;
+  return RowTriple{p[0], lane < C ? p[1] : 0.f, p[2]};
+}
+__device__ __forceinline__ float row_entropy(const RowTriple& t0, const float* __restrict__ part,
+                                             int C, int b) {
   const int lane = threadIdx.x & 63;
   const float* pr = part + static_cast<long long>(b) * C * 3;
-  const int i0 = min(lane, C - 1);
-  const float m0 = pr[3 * i0], s0 = lane < C ? pr[3 * i0 + 1] : 0.f, w0 = pr[3 * i0 + 2];
+  const float m0 = t0.m, s0 = t0.s, w0 = t0.w;
   float mloc = m0;
   for (int i = lane + 64; i < C; i += 64) mloc = fmaxf(mloc, pr[3 * i]);
   const float MG = wave_max(mloc);
@@ -180,6 +188,10 @@ __device__ __forceinline__ float row_entropy(const float* __restrict__ part, int
 #pragma clang fp contract(off)
     return (log2f(s) - w / s) * kLn2;
   }
+}
+
+__device__ __forceinline__ float row_entropy(const float* __restrict__ part, int C, int b) {
+  return row_entropy(row_triple(part, C, b), part, C, b);
 }
 
 // The controller's state of sequence b, loaded before its entropy is formed
