@@ -370,7 +370,11 @@ constexpr int kBinMaxima4 = 8;        // float4 of maxima per thread, at most (v
 constexpr int kBinCap = 1024;         // maxima at the edge, and tokens listed, at most
 static_assert(ENT_EST_MAX_K <= kBinCap / 2, "room above the k-th maximum");
 constexpr float kBinsPerUnit = 32.f;  // bins per doubling
-__device__ __forceinline__ float est_bin_pos(float v, float M) {   // monotone in v; M: 2048
+// Position of scaled logit v: monotone in v; M: 2048.  A token's v is the
+// rounded product that the chunk pass formed (no contraction into v - M), so
+// a thread's largest token lies exactly where its maximum was counted.
+__device__ __forceinline__ float est_bin_pos(float v, float M) {
+#pragma clang fp contract(off)
   return (v - M) * kBinsPerUnit + static_cast<float>(kEstBins);
 }
 
@@ -457,21 +461,23 @@ __device__ __forceinline__ bool est_binned(int est, int k, const float* __restri
   const float fe = static_cast<float>(edge);
   unsigned* val = lds;
   int* qual = reinterpret_cast<int*>(lds + slots / 2);
-  int n = 0, total;
-#pragma unroll
-  for (int u = 0; u < kBinMaxima4; ++u) {
-    n += est_bin_pos(v[u].x, M) >= fe;
-    n += est_bin_pos(v[u].y, M) >= fe;
-    n += est_bin_pos(v[u].z, M) >= fe;
-    n += est_bin_pos(v[u].w, M) >= fe;
-  }
-  int o = est_block_offset(n, sh, total);
+  // Each list entry is decided once, as a bit of a mask: the places a thread
+  // reserves are the ones it writes.
+  static_assert(4 * kBinMaxima4 <= 32, "a bit per maximum");
+  unsigned in = 0;
+  int total;
 #pragma unroll
   for (int u = 0; u < kBinMaxima4; ++u) {
     const float e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
+    for (int c = 0; c < 4; ++c) in |= (est_bin_pos(e[c], M) >= fe ? 1u : 0u) << (4 * u + c);
+  }
+  int o = est_block_offset(__popc(in), sh, total);
+#pragma unroll
+  for (int u = 0; u < kBinMaxima4; ++u) {
+#pragma unroll
     for (int c = 0; c < 4; ++c)
-      if (est_bin_pos(e[c], M) >= fe) qual[o++] = 4 * (t + u * kBinThreads) + c;
+      if (in >> (4 * u + c) & 1u) qual[o++] = 4 * (t + u * kBinThreads) + c;
   }
   __syncthreads();
   // The qualifying threads' logits, four of the 16 at a time, with the chunk
@@ -494,17 +500,18 @@ __device__ __forceinline__ bool est_binned(int est, int k, const float* __restri
       }
     }
   }
-  n = 0;
+  static_assert(4 * kItems <= 32, "a bit per token");
+  in = 0;
 #pragma unroll
   for (int u = 0; u < kItems; ++u) {
     if (u * kBinThreads >= 4 * nq) break;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       z[u][c] *= c2;
-      n += est_bin_pos(z[u][c], M) >= fe;
+      in |= (est_bin_pos(z[u][c], M) >= fe ? 1u : 0u) << (4 * u + c);
     }
   }
-  o = est_block_offset(n, sh, total);
+  o = est_block_offset(__popc(in), sh, total);
   const int a = total;                     // tokens at or above the edge: at least nq >= k
   if (a > cap) {
     __syncthreads();
@@ -515,7 +522,7 @@ __device__ __forceinline__ bool est_binned(int est, int k, const float* __restri
     if (u * kBinThreads >= 4 * nq) break;
 #pragma unroll
     for (int c = 0; c < 4; ++c)
-      if (est_bin_pos(z[u][c], M) >= fe) val[o++] = est_key(z[u][c]);
+      if (in >> (4 * u + c) & 1u) val[o++] = est_key(z[u][c]);
   }
   if (t < 4 && a + t < ((a + 3) & ~3)) val[a + t] = 0u;     // below every key
   __syncthreads();
