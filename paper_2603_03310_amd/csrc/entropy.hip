@@ -9,7 +9,7 @@ namespace {
 
 // One workgroup per row: the top-k or tail-corrected estimate from the chunk
 // triples, the thread maxima and the re-read logits, then the controller.
-constexpr int kEstFinalizeThreads = 512;
+constexpr int kEstFinalizeThreads = kBinThreads;
 
 __global__ __launch_bounds__(kEstFinalizeThreads) void estimate_finalize_kernel(
     int est, int k, int V, int C, const float* __restrict__ part, const float* __restrict__ tmax,

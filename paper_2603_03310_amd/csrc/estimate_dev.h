@@ -26,11 +26,9 @@
 //     above theta1 plus copies of theta1.
 // Both selections are exact radix selects (11-bit digits over the bits in
 // which the keys differ); the second counts only the values above theta1.
-// Every thread of the workgroup takes part in the selections, whose results
-// do not depend on the workgroup size; the qualifying threads are listed in
-// ascending order and the first kEstThreads threads form the sums in a fixed
-// order, so every caller (the per-stage kernel, the fused step in either
-// form) gets the same float.
+// Workgroups of kBinThreads threads; the qualifying threads are listed in
+// ascending order and the sums formed in a fixed order, so every caller (the
+// per-stage kernel, the fused step in either form) gets the same float.
 //
 // That is the general path; most rows need neither radix select.  theta1 may be any lower bound that
 // at least k maxima reach and not many more do: est_binned counts the maxima
@@ -47,7 +45,7 @@
 namespace ent {
 namespace {
 
-constexpr int kEstThreads = 256;   // threads that form the sums (every caller has them)
+constexpr int kEstThreads = 256;   // threads that form the general path's sums
 constexpr int kEstWaves = kEstThreads / 64;
 constexpr int kEstMaxWaves = 16;   // workgroups of up to 1024 threads
 constexpr int kEstLds1 = 8192;     // thread maxima staged in LDS (more: read from memory)
@@ -584,16 +582,15 @@ __device__ __forceinline__ bool est_binned(int est, int k, const float* __restri
 // the caller takes the exact entropy when k >= |V|).  part: the chunk
 // triples; tmax: the chunk threads' maxima [B, C, 256]; T: the row's
 // temperature (the chunk pass's); lds: est_lds_bytes(C, k) of dynamic LDS,
-// 16-byte aligned.  Every thread of the workgroup (a multiple of 64, from
-// kEstThreads to 1024) calls it; the result, in every thread, does not
-// depend on the workgroup size.
+// 16-byte aligned.  Workgroups of kBinThreads threads only (the sums' order is
+// theirs), every one of which calls it; the result is in every thread.
 __device__ __forceinline__ float row_estimate(int est, int k, const float* __restrict__ part,
                                               const float* __restrict__ tmax,
                                               const float* __restrict__ logits, long long ld,
                                               int V, int C, float T, int b, unsigned* lds,
                                               EstShared& sh) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int NT = blockDim.x;
+  constexpr int NT = kBinThreads;
   const bool worker = t < kEstThreads;
   const int n1 = C * kEstChunkThreads;
   const float* tm = tmax + static_cast<long long>(b) * n1;
@@ -624,7 +621,7 @@ __device__ __forceinline__ float row_estimate(int est, int k, const float* __res
   }
 
   const float c2 = __fdiv_rn(kLog2e, T);
-  if (NT == kBinThreads && k <= n1 && n1 <= 4 * kBinMaxima4 * kBinThreads) {
+  if (k <= n1 && n1 <= 4 * kBinMaxima4 * kBinThreads) {
     float H;
     if (est_binned(est, k, tm, n1, row, V, c2, est_key_slots(C, k), lds, sh, &H)) {
       __syncthreads();                     // the LDS is the caller's again
@@ -636,7 +633,7 @@ __device__ __forceinline__ float row_estimate(int est, int k, const float* __res
   // maxima fit, all of a thread's loads issued before its stores).
   const bool in_lds = n1 <= kEstLds1;
   if (in_lds) {
-    constexpr int P4 = kEstLds1 / 4 / kEstThreads;   // float4 per thread, at most
+    constexpr int P4 = kEstLds1 / 4 / NT;            // float4 per thread, at most
     float4 v[P4];
 #pragma unroll
     for (int u = 0; u < P4; ++u) {

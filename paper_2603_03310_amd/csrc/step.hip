@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kFoldThreads) void step_b1_kernel(
     const int* __restrict__ tables, float* __restrict__ theta, int* __restrict__ kept,
     int* __restrict__ kphys, int* __restrict__ n_kept, int P, Budget bu, unsigned* flags,
     unsigned* tickets, const float2* __restrict__ ex) {
-  static_assert(kFoldThreads >= kEstThreads && kFoldThreads == kSelThreads, "workgroup size");
+  static_assert(kFoldThreads == kBinThreads && kFoldThreads == kSelThreads, "workgroup size");
   // Estimator LDS, then (the selecting workgroup) the keys and encoded blocks.
   extern __shared__ __attribute__((aligned(16))) unsigned dyn_lds[];
   __shared__ float s_pm[kFoldThreads], s_ps[kFoldThreads], sL[128];
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(kSelThreads) void step_b_kernel(
     float* __restrict__ theta, int* __restrict__ kept, int* __restrict__ kphys,
     int* __restrict__ n_kept, int MAXB, int P, int nch_max, int Hq, Budget bu, unsigned* flags,
     SampleArgs sa, int est, int est_k, const float* __restrict__ tmax) {
-  static_assert(kSelThreads >= kSampleThreads && kSelThreads >= kEstThreads, "workgroup size");
+  static_assert(kSelThreads >= kSampleThreads && kSelThreads == kBinThreads, "workgroup size");
   extern __shared__ __attribute__((aligned(16))) unsigned keys[];   // [MAXB] keys, [MAXB] blocks, estimator
   __shared__ SelectShared sh;
   __shared__ SampleShared ssh;
