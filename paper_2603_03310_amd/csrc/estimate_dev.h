@@ -30,14 +30,17 @@
 // ascending order and the sums formed in a fixed order, so every caller (the
 // per-stage kernel, the fused step in either form) gets the same float.
 //
-// That is the general path; most rows need neither radix select.  theta1 may be any lower bound that
-// at least k maxima reach and not many more do: est_binned counts the maxima
-// in 2048 linear bins below the row's maximum (one LDS pass), takes the edge
-// of the bin in which the k-th lies, re-reads the 16 logits of each maximum
-// at or above it, lists the tokens at or above the edge, and finds the k-th
-// largest of those few hundred by counting ranks.  Rows that do not suit the
-// bins (fewer than k maxima within 64 doublings of the top, more than 1024 at
-// the edge, NaN or infinite logits) take the general path.
+// That is the general path; most rows need neither radix select.  theta1 may
+// be any lower bound that at least k maxima reach and not many more do:
+// est_binned counts the maxima in 2048 linear bins below the row's maximum
+// (one LDS pass), takes the edge of the bin in which the k-th lies, re-reads
+// the 16 logits of each maximum at or above it, lists the tokens at or above
+// the edge, and finds the k-th largest of those few hundred by counting ranks
+// (past 512 of them by a radix select).  Ties: with k maxima equal to the
+// row's the estimate needs no token, and with many at the edge, the least of
+// them the k-th, only the tokens above it are listed.  Rows that do not suit
+// the bins (fewer than k maxima within 64 doublings of the top, more than 1024
+// at the edge that are no ties, NaN or infinite logits) take the general path.
 #pragma once
 
 #include "entropy_dev.h"
@@ -229,18 +232,18 @@ __device__ __forceinline__ unsigned est_kth_largest(const Src& src, int n4, unsi
         const unsigned krem = static_cast<unsigned>(sh.krem);
         const unsigned above = suf - cl;
         if (above < krem && suf >= krem) {
-          unsigned run = above;
+          // (No early exit: with one the compiler kept its 32 conditions in
+          // scalar registers and spilled them.)
+          unsigned run = above, before = above;
           int d = BPL * lane;
 #pragma unroll
           for (int j = BPL - 1; j >= 0; --j) {
-            if (run + c[j] >= krem) {
-              d = BPL * lane + j;
-              break;
-            }
+            d = run < krem ? BPL * lane + j : d;
+            before = run < krem ? run : before;
             run += c[j];
           }
           sh.digit = d;
-          sh.krem = static_cast<int>(krem - run);
+          sh.krem = static_cast<int>(krem - before);
         }
       }
       __syncthreads();
@@ -360,20 +363,26 @@ __device__ __forceinline__ float est_entropy(int est, int k, int V, unsigned the
 // threads, every one of which must call it.  True: *H is the estimate (in
 // every thread); false: the row needs the general path, whose LDS it left
 // free.  It is latency: one pass over the maxima, one round trip for the
-// re-read logits, ten barriers.  On the 8B step (64 rows of 128256 logits,
-// k = 256) the launch with the estimate takes 25 us against 36 with the radix
-// selects, the step 244.6 against 255.5.
+// re-read logits, ten barriers.  us for 64 rows of 128256 logits, entropy pass
+// and controller, k = 256, radix selects -> binned: N(0, 2) logits 35.9 -> 23.0,
+// rounded to bf16 37.2 -> 24.0, N(0, 0.01) 35.5 -> 23.6, rounded to whole
+// numbers 31.2 -> 23.6, clipped at 1.5 sigma 38.7 -> 18.7, all equal 48.6 ->
+// 21.3; N(0, 4) at T = 0.05, which the bins refuse, 34.4 -> 31.7 in all.
 constexpr int kBinThreads = 512;
 constexpr int kBinMaxima4 = 8;        // float4 of maxima per thread, at most (vocab <= 262144)
 constexpr int kBinCap = 1024;         // maxima at the edge, and tokens listed, at most
 static_assert(ENT_EST_MAX_K <= kBinCap / 2, "room above the k-th maximum");
-constexpr float kBinsPerUnit = 32.f;  // bins per doubling
+// Bins per doubling, at least; where the finite maxima span fewer than 64
+// doublings the bins divide their span, so that flat rows are resolved too
+// (the N(0, 0.01) rows above, all in the top bin otherwise, took 43.9 us).
+constexpr float kBinsPerUnit = 32.f, kMaxBinsPerUnit = 1e30f;
+constexpr int kBinTied = 128;         // maxima past the k-th at the edge: perhaps ties
 // Position of scaled logit v: monotone in v; M: 2048.  A token's v is the
 // rounded product that the chunk pass formed (no contraction into v - M), so
 // a thread's largest token lies exactly where its maximum was counted.
-__device__ __forceinline__ float est_bin_pos(float v, float M) {
+__device__ __forceinline__ float est_bin_pos(float v, float M, float scale) {
 #pragma clang fp contract(off)
-  return (v - M) * kBinsPerUnit + static_cast<float>(kEstBins);
+  return (v - M) * scale + static_cast<float>(kEstBins);
 }
 
 // Exclusive offset of this thread's n among the workgroup's, in thread order,
@@ -393,31 +402,51 @@ __device__ __forceinline__ int est_block_offset(int n, EstShared& sh, int& total
   return off;
 }
 
-__device__ __forceinline__ bool est_binned(int est, int k, const float* __restrict__ tm, int n1,
+// v: the row's n1 maxima, float4 t + u kBinThreads in v[u] (-inf past n1).
+__device__ __forceinline__ bool est_binned(int est, int k, const float4 (&v)[kBinMaxima4], int n1,
                                            const float* __restrict__ row, int V, float c2, int slots,
                                            unsigned* lds, EstShared& sh, float* H) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  float4 v[kBinMaxima4];
+  const int nu = (n1 / 4 + kBinThreads - 1) / kBinThreads;   // registers of v in use
+  for (int i = t; i < kEstBins; i += kBinThreads) sh.hist[i] = 0u;
+  if (t == 0) {
+    sh.digit = -1;
+    sh.ncand = 0;
+  }
+  float lo = INFINITY, hi = -INFINITY;     // least finite maximum, this thread's largest
 #pragma unroll
   for (int u = 0; u < kBinMaxima4; ++u) {
-    const int i4 = t + u * kBinThreads;
-    v[u] = i4 < n1 / 4 ? reinterpret_cast<const float4*>(tm)[i4]
-                       : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    if (u >= nu) break;
+    const float e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) lo = fminf(lo, e[c] > -INFINITY ? e[c] : INFINITY);
+    hi = fmaxf(hi, fmaxf(fmaxf(e[0], e[1]), fmaxf(e[2], e[3])));
   }
-  for (int i = t; i < kEstBins; i += kBinThreads) sh.hist[i] = 0u;
-  if (t == 0) sh.digit = -1;
+  lo = -wave_max(-lo);
+  if (lane == 0) sh.fred[wave] = lo;
   __syncthreads();                         // the bins are clear; M and S of wave 0 are there
   const float M = sh.M, S = sh.S;
+#pragma unroll
+  for (int i = 0; i < kBinThreads / 64; ++i) lo = fminf(lo, sh.fred[i]);
   if (sh.odd) return false;
+  const float scale =
+      fminf(fmaxf(static_cast<float>(kEstBins - 1) / (M - lo), kBinsPerUnit), kMaxBinsPerUnit);
 #pragma unroll
   for (int u = 0; u < kBinMaxima4; ++u) {
-    if (u * kBinThreads >= n1 / 4) break;
+    if (u >= nu) break;
     const float e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const float x = est_bin_pos(e[c], M);
+      const float x = est_bin_pos(e[c], M, scale);
       if (x >= 0.f) atomicAdd(&sh.hist[min(static_cast<int>(x), kEstBins - 1)], 1u);
     }
+  }
+  if (hi == M) {                           // few threads, but for ties
+    int n = 0;
+#pragma unroll
+    for (int u = 0; u < kBinMaxima4; ++u)
+      n += (v[u].x == M) + (v[u].y == M) + (v[u].z == M) + (v[u].w == M);
+    atomicAdd(&sh.ncand, n);
   }
   __syncthreads();
   if (wave == 0) {
@@ -449,30 +478,69 @@ __device__ __forceinline__ bool est_binned(int est, int k, const float* __restri
     }
   }
   __syncthreads();
-  const int edge = sh.digit, nq = sh.nq;
-  const int cap = min(slots / 2, kBinCap);
-  if (edge < 0 || nq > cap) {
+  const int edge = sh.digit, cap = min(slots / 2, kBinCap);
+  int nq = sh.nq;
+  // Clipped, saturated or equal logits: the top k are all M.
+  if (sh.ncand >= k) {
+    *H = est_entropy(est, k, V, est_key(M), 0, 0.f, 0.f, M, S);
+    return true;
+  }
+  if (edge < 0) {
     __syncthreads();                       // both read before they are written again
     return false;
   }
-  // x < 2048 at bins below the top one: x >= edge is the test for all of them.
-  const float fe = static_cast<float>(edge);
-  unsigned* val = lds;
-  int* qual = reinterpret_cast<int*>(lds + slots / 2);
-  // Each list entry is decided once, as a bit of a mask: the places a thread
-  // reserves are the ones it writes.
+  // The maxima in the k-th's bin and above, each decided once (a bit of a
+  // mask: the places a thread reserves are the ones it writes).
   static_assert(4 * kBinMaxima4 <= 32, "a bit per maximum");
+  const float fe = static_cast<float>(edge);
   unsigned in = 0;
-  int total;
 #pragma unroll
   for (int u = 0; u < kBinMaxima4; ++u) {
+    if (u >= nu) break;
     const float e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
-    for (int c = 0; c < 4; ++c) in |= (est_bin_pos(e[c], M) >= fe ? 1u : 0u) << (4 * u + c);
+    for (int c = 0; c < 4; ++c) in |= (est_bin_pos(e[c], M, scale) >= fe ? 1u : 0u) << (4 * u + c);
   }
-  int o = est_block_offset(__popc(in), sh, total);
+  bool strict = false;
+  float thr = INFINITY;
+  if (nq > min(k + kBinTied, cap)) {
+    // Many at the edge.  If fewer than k maxima exceed the least of them, thr,
+    // that is the k-th, and only the tokens above it are wanted.
+#pragma unroll
+    for (int u = 0; u < kBinMaxima4; ++u) {
+      if (u >= nu) break;
+      const float e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) thr = in >> (4 * u + c) & 1u ? fminf(thr, e[c]) : thr;
+    }
+    thr = -wave_max(-thr);
+    if (lane == 0) sh.fred[kEstMaxWaves + wave] = thr;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kBinThreads / 64; ++i) thr = fminf(thr, sh.fred[kEstMaxWaves + i]);
+    unsigned gt = 0;
+#pragma unroll
+    for (int u = 0; u < kBinMaxima4; ++u) {
+      if (u >= nu) break;
+      const float e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) gt |= (e[c] > thr ? 1u : 0u) << (4 * u + c);
+    }
+    const int n_above = est_block_count(__popc(gt), sh);
+    if (n_above < k) {
+      strict = true;
+      in = gt;
+      nq = n_above;
+    } else if (nq > cap) {
+      return false;
+    }
+  }
+  int total, o = est_block_offset(__popc(in), sh, total);
+  unsigned* val = lds;
+  int* qual = reinterpret_cast<int*>(lds + slots / 2);
 #pragma unroll
   for (int u = 0; u < kBinMaxima4; ++u) {
+    if (u >= nu) break;
 #pragma unroll
     for (int c = 0; c < 4; ++c)
       if (in >> (4 * u + c) & 1u) qual[o++] = 4 * (t + u * kBinThreads) + c;
@@ -506,11 +574,11 @@ __device__ __forceinline__ bool est_binned(int est, int k, const float* __restri
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       z[u][c] *= c2;
-      in |= (est_bin_pos(z[u][c], M) >= fe ? 1u : 0u) << (4 * u + c);
+      in |= ((strict ? z[u][c] > thr : est_bin_pos(z[u][c], M, scale) >= fe) ? 1u : 0u) << (4 * u + c);
     }
   }
   o = est_block_offset(__popc(in), sh, total);
-  const int a = total;                     // tokens at or above the edge: at least nq >= k
+  const int a = total;                     // (at least nq: a maximum is a token's rounded t)
   if (a > cap) {
     __syncthreads();
     return false;
@@ -524,34 +592,42 @@ __device__ __forceinline__ bool est_binned(int est, int k, const float* __restri
   }
   if (t < 4 && a + t < ((a + 3) & ~3)) val[a + t] = 0u;     // below every key
   __syncthreads();
-  // Each listed token counts those above it; the k-th largest is the least
-  // token with fewer than k above it.
-  unsigned mine[kBinCap / kBinThreads], least = 0xFFFFFFFFu;
-  int gt[kBinCap / kBinThreads];
+  unsigned mine[kBinCap / kBinThreads], theta;
 #pragma unroll
   for (int u = 0; u < kBinCap / kBinThreads; ++u) {
     const int i = t + u * kBinThreads;
     mine[u] = i < a ? val[i] : 0u;
-    gt[u] = k;
-    if (64 * wave + u * kBinThreads >= a) continue;         // uniform in the wave
-    int n = 0;
-#pragma unroll 8
-    for (int j = 0; j < (a + 3) / 4; ++j) {
-      const uint4 x = reinterpret_cast<const uint4*>(val)[j];
-      n += (x.x > mine[u]) + (x.y > mine[u]) + (x.z > mine[u]) + (x.w > mine[u]);
-    }
-    gt[u] = i < a ? n : k;
-    if (gt[u] < k) least = min(least, mine[u]);
   }
-  least = wave_min_u(least);
-  if (lane == 0) sh.red[wave] = least;
-  __syncthreads();
-  unsigned theta = sh.red[0];
+  int n_gt = 0;
+  if (a < k) {
+    theta = est_key(thr);                  // (strict: fewer than k tokens above the k-th maximum)
+    if (t == 0) sh.rgt = a;
+  } else if (a <= kBinThreads) {
+    // Each listed token counts those above it; the k-th largest is the least
+    // token with fewer than k above it.
+    unsigned least = 0xFFFFFFFFu;
+    int gt = k;
+    if (64 * wave < a) {                                    // uniform in the wave
+      int n = 0;
+#pragma unroll 8
+      for (int j = 0; j < (a + 3) / 4; ++j) {
+        const uint4 x = reinterpret_cast<const uint4*>(val)[j];
+        n += (x.x > mine[0]) + (x.y > mine[0]) + (x.z > mine[0]) + (x.w > mine[0]);
+      }
+      gt = t < a ? n : k;
+      if (gt < k) least = mine[0];
+    }
+    least = wave_min_u(least);
+    if (lane == 0) sh.red[wave] = least;
+    __syncthreads();
+    theta = sh.red[0];
 #pragma unroll
-  for (int i = 1; i < kBinThreads / 64; ++i) theta = min(theta, sh.red[i]);
-#pragma unroll
-  for (int u = 0; u < kBinCap / kBinThreads; ++u)
-    if (gt[u] < k && mine[u] == theta) sh.rgt = gt[u];      // the same number from each
+    for (int i = 1; i < kBinThreads / 64; ++i) theta = min(theta, sh.red[i]);
+    if (gt < k && mine[0] == theta) sh.rgt = gt;            // the same number from each
+  } else {
+    theta = est_kth_largest<EstLdsKeys, true>(EstLdsKeys{val}, (a + 3) / 4, 1u, k, sh, n_gt);
+    if (t == 0) sh.rgt = n_gt;
+  }
   float s = 0.f, w = 0.f;
 #pragma unroll
   for (int u = 0; u < kBinCap / kBinThreads; ++u)
@@ -598,6 +674,16 @@ __device__ __forceinline__ float row_estimate(int est, int k, const float* __res
   unsigned* keys = lds;
   int* qual = reinterpret_cast<int*>(lds + est_key_slots(C, k));
 
+  // The maxima load before the row's triples are waited for.
+  const bool in_regs = n1 <= 4 * kBinMaxima4 * kBinThreads;
+  float4 v[kBinMaxima4];
+#pragma unroll
+  for (int u = 0; u < kBinMaxima4; ++u) {
+    const int i4 = t + u * kBinThreads;
+    v[u] = in_regs && i4 < n1 / 4 ? reinterpret_cast<const float4*>(tm)[i4]
+                                  : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+  }
+
   // Row maximum and mass from the chunk triples (as the exact entropy does).
   if (wave == 0) {
     const float* pr = part + static_cast<long long>(b) * C * 3;
@@ -621,28 +707,22 @@ __device__ __forceinline__ float row_estimate(int est, int k, const float* __res
   }
 
   const float c2 = __fdiv_rn(kLog2e, T);
-  if (k <= n1 && n1 <= 4 * kBinMaxima4 * kBinThreads) {
+  if (k <= n1 && in_regs) {
     float H;
-    if (est_binned(est, k, tm, n1, row, V, c2, est_key_slots(C, k), lds, sh, &H)) {
+    if (est_binned(est, k, v, n1, row, V, c2, est_key_slots(C, k), lds, sh, &H)) {
       __syncthreads();                     // the LDS is the caller's again
       return H;
     }
   }
 
   // Stage 1: theta1 = k-th largest thread maximum (staged in LDS when the
-  // maxima fit, all of a thread's loads issued before its stores).
+  // maxima fit).
   const bool in_lds = n1 <= kEstLds1;
+  static_assert(kEstLds1 <= 4 * kBinMaxima4 * kBinThreads, "staged maxima are in registers");
   if (in_lds) {
-    constexpr int P4 = kEstLds1 / 4 / NT;            // float4 per thread, at most
-    float4 v[P4];
 #pragma unroll
-    for (int u = 0; u < P4; ++u) {
-      const int i4 = t + u * NT;
-      v[u] = i4 < n1 / 4 ? reinterpret_cast<const float4*>(tm)[i4] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int u = 0; u < P4; ++u) {
-      const int i4 = t + u * NT;
+    for (int u = 0; u < kBinMaxima4; ++u) {
+      const int i4 = t + u * kBinThreads;
       if (i4 < n1 / 4)
         reinterpret_cast<uint4*>(keys)[i4] =
             make_uint4(est_key(v[u].x), est_key(v[u].y), est_key(v[u].z), est_key(v[u].w));

@@ -1,6 +1,7 @@
 """The top-k estimators over rows that suit the binned selection and rows that
-need the general one (top k spread over more than 64 doublings, thousands of
-equal logits, few finite ones; a row with a NaN runs, with no value promised), at vocabularies around the limits of the
+need the general one (top k spread over more than 64 doublings, few finite
+logits; a row with a NaN runs, with no value promised), with ties of every kind
+(equal, rounded, clipped, few threads above), at vocabularies around the limits of the
 two (row ends off 16 bytes, maxima past the LDS stage, past the registers) and
 at both ends of k.  The reference is the definition in float64."""
 import math
@@ -28,8 +29,12 @@ def _rows(torch, V):
     few[:: max(1, V // 40)] = 2.0 * n[:: max(1, V // 40)]
     clumped = n.clone()
     clumped[: V // 8] += 9.0
+    stacked = torch.ones_like(n)       # ties, and above them many tokens of few threads
+    for i in range(4):
+        stacked[1024 * i: 1024 * i + 160] = 3.0 + 0.25 * n[1024 * i: 1024 * i + 160]
     return [n * 0.01, n * 0.5, n * 4.0, n * 60.0, -1.2 * torch.log(ranks), spike, masked, low, few,
-            clumped, torch.zeros_like(n), torch.round(n), torch.round(40.0 * n) / 40.0]
+            clumped, torch.zeros_like(n), torch.round(n), torch.round(40.0 * n) / 40.0,
+            torch.clamp(2.0 * n, max=3.0), n.bfloat16().float(), stacked, -200.0 + 1e-2 * n]
 
 
 @pytest.mark.parametrize("k", [1, 16, 256, 512])
@@ -66,9 +71,10 @@ def test_estimate(torch_cuda, V, k):
         ref = want[est] if k < V else torch.special.entr(p).sum(1)
         # Scaled logits up to 400 carry 2^-24 of themselves into the exponent,
         # and -p ln p weighs that by at most ln V: 400 / 2^24 x 12.5 = 3e-4 at
-        # the widest row (x 60), under 1e-4 in the others (|z| <= 60).
+        # the widest rows (x 60, and those around -200), under 1e-4 in the
+        # others (|z| <= 60).
         tol = torch.full((B,), 1e-4, dtype=torch.float64, device="cuda")
-        tol[3] = 3e-4
+        tol[3] = tol[B - 2] = 3e-4
         err = (h.double() - ref).abs()[:-1]
         assert bool((err <= tol[:-1]).all()), (est, err.tolist())
 
