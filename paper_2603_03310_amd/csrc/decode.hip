@@ -72,6 +72,7 @@ struct DecodeArgs {
   int B, Hkv, G, MAXB, P;
   int W;              // waves of the decode grid
   int R;              // ranges that write partials (workgroups for bf16, waves for fp32)
+  int few;            // bf16: ranges while the units are few (few_ranges)
   int nsl;            // merge workgroups per segment
   float scale_log2;   // softmax scale times log2(e)
 };
@@ -139,15 +140,14 @@ __device__ __forceinline__ int wave_of(int x, int U, int W) {
 // range's next unit is prefetched behind the one before.  So a bf16 workgroup
 // takes at least kMinUnits units (two per wave; 4, 8 and 16 measured 27.8,
 // 27.7 and 28.6 us for the step of one 2500-token request, 38.2, 33.5 and
-// 34.6 us for nine of 301-4001 tokens), and the second workgroup per CU joins
-// only once each of the first ones has kTwoUnits (16, 32 and 64: 46.8, 44.6
+// 34.6 us for nine of 301-4001 tokens), and the grid's ranges past the first
+// `few` join only once each of those has kTwoUnits (16, 32 and 64: 46.8, 44.6
 // and 44.7 us for two of 12465-25000 tokens; without, 48.6).  Every range in
 // use holds a unit.  With all ranges in use those steps took 50.7, 38.9 and
 // 61.6 us, most of it in the merge.
 constexpr int kMinUnits = 8, kTwoUnits = 32;
-__host__ __device__ __forceinline__ int ranges_used(int U, int R) {
-  const int half = (R + 1) / 2;
-  const int cap = U < half * kTwoUnits ? half : R, need = (U + kMinUnits - 1) / kMinUnits;
+__host__ __device__ __forceinline__ int ranges_used(int U, int R, int few) {
+  const int cap = U < few * kTwoUnits ? few : R, need = (U + kMinUnits - 1) / kMinUnits;
   const int n = cap < need ? cap : need;
   return n < 1 ? 1 : n;
 }
@@ -281,18 +281,18 @@ __global__ __launch_bounds__(kThreads, 3) void decode_bf16_kernel(DecodeArgs a) 
   const int wave = threadIdx.x >> 6;
   const int w = blockIdx.x * kWaves + wave;
   zero_empty<D>(a, s_nk);
-  const int R = ranges_used(U, a.R);
+  const int R = ranges_used(U, a.R, a.few);
   if (U == 0 || blockIdx.x >= R) {
     if (threadIdx.x == 0) a.rec[blockIdx.x] = make_int2(-1, 0);
     return;
   }
-  // With fewer ranges than the grid's fewer weights are the 1 that a piece's
-  // largest one is, which bf16 holds exactly: 7% more rounding error in the
-  // outputs than with every range in use (1.63e-6 against 1.52e-6 for one
+  // With few units (in fewer, longer ranges) fewer weights are the 1 that a
+  // piece's largest one is, which bf16 holds exactly: 7% more rounding error in
+  // the outputs than with every range in use (1.63e-6 against 1.52e-6 for one
   // request).  Such steps have the matrix cores idle, so the third part of P
   // goes in too: 1.8e-7, for 0.2 us of the step (25.6 -> 25.7, nine requests
   // 30.2 -> 30.4).
-  const bool fine = R < a.R;
+  const bool fine = U < (a.R + 1) / 2 * kTwoUnits;
   const int G = a.G;
   // Cut partials of this workgroup's waves, merged in LDS at the end:
   // slot 2 i (wave i's first segment, begun before its range) and 2 i + 1
@@ -808,6 +808,17 @@ __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
 // 33.5, 9 us of 58 for two requests of 12465-25000 tokens).
 constexpr int kCombinePrefetch = 16;       // partials whose loads are issued together
 
+// Ranges while the units are few: a workgroup per CU.  Where no more than that
+// fit (G = 16 at d = 128, by LDS) half of them would leave half the CUs idle,
+// which pays only if all would cut the segments into more pieces than the
+// merge reads at once (128 heads of 128 dims, us per step, all against half:
+// 32 requests of 200 tokens 26.5 against 32.5, 9 of 700 29.8 and 31.6, 3 of
+// 2500 34.3 and 35.6; one of 2100 31.6 and 30.0, of 4000 37.3 and 34.8).
+inline int few_ranges(int R, int num_cu, int segments) {
+  if (R > num_cu) return num_cu;
+  return static_cast<long long>(segments) * kCombinePrefetch >= R ? R : (R + 1) / 2;
+}
+
 // Running (max, sum, outputs) with a partial or another running triple added.
 __device__ __forceinline__ void combine_add(float& M, float& L, f32x4_t& acc, float m, float l,
                                             f32x4_t v) {
@@ -986,12 +997,13 @@ hipError_t launch_decode(const ent_ctx* c, int B, const void* q, const void* k_c
   a.P = cf.num_pool_blocks;
   a.W = c->decode_grid * kWaves;
   a.R = cf.kv_dtype == ENT_BF16 ? c->decode_grid : a.W;
+  a.few = few_ranges(c->decode_grid, c->num_cu, B * cf.num_kv_heads);
   a.scale_log2 = cf.scale * kLog2e;
   const size_t lds = plan_lds_bytes(B);
   // No more workgroups than the ranges that the batch's tables can fill.
   const int umax = static_cast<int>(static_cast<long long>(B) * cf.max_blocks_per_seq * cf.num_kv_heads);
   const int nwg = cf.kv_dtype == ENT_BF16
-                      ? ranges_used(umax, c->decode_grid)
+                      ? ranges_used(umax, c->decode_grid, a.few)
                       : std::min(c->decode_grid, umax / kWaves + 1);
   const dim3 grid(nwg);
   if (cf.kv_dtype == ENT_BF16) {

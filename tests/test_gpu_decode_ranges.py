@@ -15,7 +15,9 @@ CASES = [
     ("bf16", 1, 8, [1]), ("bf16", 1, 4, [7]), ("bf16", 1, 4, [8]), ("bf16", 1, 4, [9]),
     ("bf16", 2, 1, [3, 0, 6, 1]), ("bf16", 1, 8, [130]), ("bf16", 8, 4, [43]),
     ("bf16", 1, 8, [8191]), ("bf16", 1, 8, [8192]), ("bf16", 4, 16, [1500, 548, 1]),
-    ("f32", 1, 1, [1]), ("f32", 2, 4, [5, 0, 30]), ("f32", 1, 2, [2049]),
+    ("bf16", 8, 16, [40, 0] + [13] * 30), ("bf16", 2, 16, [700, 600]),
+    ("f32", 1, 1, [1]), ("f32", 2, 4, [5, 0, 30]), ("f32", 1, 2, [2049]), ("f32", 2, 8, [70, 3]),
+    ("f32", 1, 16, [300, 1]),
 ]
 
 
