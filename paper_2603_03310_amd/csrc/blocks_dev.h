@@ -812,7 +812,6 @@ __device__ __forceinline__ void select_core(unsigned* keys, const int* tbl, int 
   const int per = (rows + kSelWaves - 1) / kSelWaves;
   const int r0 = wave * per, r1 = min(r0 + per, rows);
   int mine = 0;
-#pragma unroll 4
   for (int r = r0; r < r1; ++r) {
     const int i = 64 * r + lane;
     mine += __popcll(__ballot(i < nb && keys[min(i, nb - 1)] >= tkey));
@@ -827,7 +826,6 @@ __device__ __forceinline__ void select_core(unsigned* keys, const int* tbl, int 
   }
   int* krow = kept + static_cast<long long>(b) * MAXB;
   int* prow = kphys + static_cast<long long>(b) * MAXB;
-#pragma unroll 4
   for (int r = r0; r < r1; ++r) {
     const int i = 64 * r + lane;
     const bool f = i < nb && keys[min(i, nb - 1)] >= tkey;
