@@ -36,11 +36,12 @@
 // (one LDS pass), takes the edge of the bin in which the k-th lies, re-reads
 // the 16 logits of each maximum at or above it, lists the tokens at or above
 // the edge, and finds the k-th largest of those few hundred by counting ranks
-// (past 512 of them by a radix select).  Ties: with k maxima equal to the
-// row's the estimate needs no token, and with many at the edge, the least of
-// them the k-th, only the tokens above it are listed.  Rows that do not suit
-// the bins (fewer than k maxima within 64 doublings of the top, more than 1024
-// at the edge that are no ties, NaN or infinite logits) take the general path.
+// (past 512 of them by a radix select).  Flat and tied rows have many maxima
+// in that bin: the bins then divide what those span, or, where the k-th
+// maximum is one of many equal ones, only the tokens above it are listed.
+// Rows that do not suit the bins (fewer than k maxima within 64 doublings of
+// the top, more than 1024 at the edge that are no ties, NaN or infinite
+// logits) take the general path.
 #pragma once
 
 #include "entropy_dev.h"
@@ -237,11 +238,12 @@ __device__ __forceinline__ unsigned est_kth_largest(const Src& src, int n4, unsi
           unsigned run = above, before = above;
           int d = BPL * lane;
 #pragma unroll
-          for (int j = BPL - 1; j >= 0; --j) {
-            d = run < krem ? BPL * lane + j : d;
-            before = run < krem ? run : before;
-            run += c[j];
-          }
+          for (int j = BPL - 1; j >= 0; --j)
+            if (run < krem) {
+              before = run;
+              run += c[j];
+              d = BPL * lane + j;
+            }
           sh.digit = d;
           sh.krem = static_cast<int>(krem - before);
         }
@@ -363,20 +365,23 @@ __device__ __forceinline__ float est_entropy(int est, int k, int V, unsigned the
 // threads, every one of which must call it.  True: *H is the estimate (in
 // every thread); false: the row needs the general path, whose LDS it left
 // free.  It is latency: one pass over the maxima, one round trip for the
-// re-read logits, ten barriers.  us for 64 rows of 128256 logits, entropy pass
-// and controller, k = 256, radix selects -> binned: N(0, 2) logits 35.9 -> 23.0,
-// rounded to bf16 37.2 -> 24.0, N(0, 0.01) 35.5 -> 23.6, rounded to whole
-// numbers 31.2 -> 23.6, clipped at 1.5 sigma 38.7 -> 18.7, all equal 48.6 ->
-// 21.3; N(0, 4) at T = 0.05, which the bins refuse, 34.4 -> 31.7 in all.
+// re-read logits, nine barriers.  us for 64 rows of 128256 logits, entropy pass
+// and controller, k = 256, radix selects -> binned: N(0, 2) logits 36.1 -> 22.0,
+// rounded to bf16 37.3 -> 22.2, N(0, 0.01) 35.5 -> 32.1, rounded to whole
+// numbers 31.2 -> 24.2, clipped at 1.5 sigma 38.6 -> 23.7, all equal 48.6 ->
+// 25.8; N(0, 4) at T = 0.05, which the bins refuse, 34.5 -> 31.4 in all.
 constexpr int kBinThreads = 512;
 constexpr int kBinMaxima4 = 8;        // float4 of maxima per thread, at most (vocab <= 262144)
 constexpr int kBinCap = 1024;         // maxima at the edge, and tokens listed, at most
 static_assert(ENT_EST_MAX_K <= kBinCap / 2, "room above the k-th maximum");
-// Bins per doubling, at least; where the finite maxima span fewer than 64
-// doublings the bins divide their span, so that flat rows are resolved too
-// (the N(0, 0.01) rows above, all in the top bin otherwise, took 43.9 us).
+// Bins per doubling (on the bins' second use, what resolves their span).
 constexpr float kBinsPerUnit = 32.f, kMaxBinsPerUnit = 1e30f;
-constexpr int kBinTied = 128;         // maxima past the k-th at the edge: perhaps ties
+// Maxima past the k-th in its bin and above that call for a second look
+// (est_refine, about 8 us): without it the N(0, 0.01) rows above, all in the
+// top bin, took 43.9 us, the whole numbers, 780 maxima at the edge, 42.5.  For
+// every row (the bins' span from all the maxima, ties counted apart) it cost
+// the N(0, 2) rows 0.4 to 1 us.
+constexpr int kBinTied = 128;
 // Position of scaled logit v: monotone in v; M: 2048.  A token's v is the
 // rounded product that the chunk pass formed (no contraction into v - M), so
 // a thread's largest token lies exactly where its maximum was counted.
@@ -402,35 +407,104 @@ __device__ __forceinline__ int est_block_offset(int n, EstShared& sh, int& total
   return off;
 }
 
-// v: the row's n1 maxima, float4 t + u kBinThreads in v[u] (-inf past n1).
-__device__ __forceinline__ bool est_binned(int est, int k, const float4 (&v)[kBinMaxima4], int n1,
+// By wave 0: the bin of the k-th largest counted value (sh.digit, left alone if
+// fewer are counted) and the number of values in it and above (sh.nq); tops
+// more values in the top bin than its counter has.  Lane l
+// holds bins BPL l .. BPL l + BPL - 1; suffix sums over the lanes.
+__device__ __forceinline__ void est_bin_find(int k, int tops, EstShared& sh) {
+  constexpr int BPL = kEstBins / 64;
+  const int lane = threadIdx.x & 63;
+  unsigned c[BPL], cl = 0;
+#pragma unroll
+  for (int j = 0; j < BPL; j += 4) {
+    const uint4 h = *reinterpret_cast<const uint4*>(&sh.hist[BPL * lane + j]);
+    c[j] = h.x;
+    c[j + 1] = h.y;
+    c[j + 2] = h.z;
+    c[j + 3] = h.w;
+    cl += h.x + h.y + h.z + h.w;
+  }
+  if (lane == 63) {
+    c[BPL - 1] += static_cast<unsigned>(tops);
+    cl += static_cast<unsigned>(tops);
+  }
+  const unsigned incl = wave_scan_u(cl);
+  const unsigned suf = lane_at(static_cast<int>(incl), 63) - incl + cl;
+  const unsigned above = suf - cl, kk = static_cast<unsigned>(k);
+  if (above < kk && suf >= kk) {
+    unsigned run = above;
+#pragma unroll
+    for (int j = BPL - 1; j >= 0; --j)
+      if (run < kk) {
+        run += c[j];
+        if (run >= kk) sh.digit = BPL * lane + j;
+      }
+    sh.nq = static_cast<int>(run);
+  }
+}
+
+// Flat and tied rows, with more than kBinTied maxima past the k-th in its bin
+// and above.  If fewer than k maxima exceed the least of them, or k maxima
+// equal M, that is the k-th, thr, and only what exceeds it is wanted (strict);
+// else the bins divide what they span.  True: scale, edge and nq are of the new bins (nq at most
+// cap), or strict, thr and nq < k; false: the general path.  The maxima are
+// read again: held in registers they would cost the other rows theirs.
+__device__ __forceinline__ bool est_refine(int k, const float* __restrict__ tm, int n1, float M,
+                                           int cap, EstShared& sh, float& scale, int& edge, int& nq,
+                                           float& thr, bool& strict) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const float fe = static_cast<float>(edge);
+  float lo = INFINITY;
+#pragma unroll 4
+  for (int i = t; i < n1; i += kBinThreads) {
+    const float e = tm[i];
+    lo = est_bin_pos(e, M, scale) >= fe ? fminf(lo, e) : lo;
+  }
+  lo = -wave_max(-lo);
+  if (lane == 0) sh.fred[wave] = lo;
+  for (int i = t; i < kEstBins; i += kBinThreads) sh.hist[i] = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kBinThreads / 64; ++i) lo = fminf(lo, sh.fred[i]);
+  scale = fminf(static_cast<float>(kEstBins - 1) / (M - lo), kMaxBinsPerUnit);
+  int n = 0;                               // above lo, and from bit 16 on equal to M
+  static_assert(4 * kBinMaxima4 * kBinThreads < (1 << 15), "two counts in one");
+#pragma unroll 4
+  for (int i = t; i < n1; i += kBinThreads) {
+    const float e = tm[i], x = est_bin_pos(e, M, scale);
+    n += (e > lo ? 1 : 0) + (e == M ? 1 << 16 : 0);
+    if (x >= 0.f && e != M) atomicAdd(&sh.hist[min(static_cast<int>(x), kEstBins - 1)], 1u);
+  }
+  n = est_block_count(n, sh);
+  const int tops = n >> 16;
+  const bool top = tops >= k;
+  n &= 0xffff;
+  if (top || n < k) {
+    thr = top ? M : lo;
+    strict = true;
+    nq = top ? 0 : n;
+    return true;
+  }
+  if (wave == 0) est_bin_find(k, tops, sh);          // (there is one: n >= k are counted)
+  __syncthreads();
+  edge = sh.digit;
+  nq = sh.nq;
+  __syncthreads();                         // both read before they are written again
+  return nq <= cap;
+}
+
+// v: the row's n1 maxima tm, float4 t + u kBinThreads in v[u] (-inf past n1).
+__device__ __forceinline__ bool est_binned(int est, int k, const float4 (&v)[kBinMaxima4], const float* __restrict__ tm, int n1,
                                            const float* __restrict__ row, int V, float c2, int slots,
                                            unsigned* lds, EstShared& sh, float* H) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int nu = (n1 / 4 + kBinThreads - 1) / kBinThreads;   // registers of v in use
+  float scale = kBinsPerUnit;
   for (int i = t; i < kEstBins; i += kBinThreads) sh.hist[i] = 0u;
-  if (t == 0) {
-    sh.digit = -1;
-    sh.ncand = 0;
-  }
-  float lo = INFINITY, hi = -INFINITY;     // least finite maximum, this thread's largest
-#pragma unroll
-  for (int u = 0; u < kBinMaxima4; ++u) {
-    if (u >= nu) break;
-    const float e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-    for (int c = 0; c < 4; ++c) lo = fminf(lo, e[c] > -INFINITY ? e[c] : INFINITY);
-    hi = fmaxf(hi, fmaxf(fmaxf(e[0], e[1]), fmaxf(e[2], e[3])));
-  }
-  lo = -wave_max(-lo);
-  if (lane == 0) sh.fred[wave] = lo;
+  if (t == 0) sh.digit = -1;
   __syncthreads();                         // the bins are clear; M and S of wave 0 are there
   const float M = sh.M, S = sh.S;
-#pragma unroll
-  for (int i = 0; i < kBinThreads / 64; ++i) lo = fminf(lo, sh.fred[i]);
   if (sh.odd) return false;
-  const float scale =
-      fminf(fmaxf(static_cast<float>(kEstBins - 1) / (M - lo), kBinsPerUnit), kMaxBinsPerUnit);
 #pragma unroll
   for (int u = 0; u < kBinMaxima4; ++u) {
     if (u >= nu) break;
@@ -441,98 +515,40 @@ __device__ __forceinline__ bool est_binned(int est, int k, const float4 (&v)[kBi
       if (x >= 0.f) atomicAdd(&sh.hist[min(static_cast<int>(x), kEstBins - 1)], 1u);
     }
   }
-  if (hi == M) {                           // few threads, but for ties
-    int n = 0;
-#pragma unroll
-    for (int u = 0; u < kBinMaxima4; ++u)
-      n += (v[u].x == M) + (v[u].y == M) + (v[u].z == M) + (v[u].w == M);
-    atomicAdd(&sh.ncand, n);
-  }
   __syncthreads();
-  if (wave == 0) {
-    // Lane l holds bins BPL l .. BPL l + BPL - 1: the bin of the k-th largest
-    // by suffix sums over the lanes.
-    constexpr int BPL = kEstBins / 64;
-    unsigned c[BPL], cl = 0;
-#pragma unroll
-    for (int j = 0; j < BPL; j += 4) {
-      const uint4 h = *reinterpret_cast<const uint4*>(&sh.hist[BPL * lane + j]);
-      c[j] = h.x;
-      c[j + 1] = h.y;
-      c[j + 2] = h.z;
-      c[j + 3] = h.w;
-      cl += h.x + h.y + h.z + h.w;
-    }
-    const unsigned incl = wave_scan_u(cl);
-    const unsigned suf = lane_at(static_cast<int>(incl), 63) - incl + cl;
-    const unsigned above = suf - cl, kk = static_cast<unsigned>(k);
-    if (above < kk && suf >= kk) {
-      unsigned run = above;
-#pragma unroll
-      for (int j = BPL - 1; j >= 0; --j)
-        if (run < kk) {
-          run += c[j];
-          if (run >= kk) sh.digit = BPL * lane + j;
-        }
-      sh.nq = static_cast<int>(run);       // maxima at or above that bin
-    }
-  }
+  if (wave == 0) est_bin_find(k, 0, sh);
   __syncthreads();
-  const int edge = sh.digit, cap = min(slots / 2, kBinCap);
-  int nq = sh.nq;
-  // Clipped, saturated or equal logits: the top k are all M.
-  if (sh.ncand >= k) {
-    *H = est_entropy(est, k, V, est_key(M), 0, 0.f, 0.f, M, S);
-    return true;
-  }
+  int edge = sh.digit, nq = sh.nq;
   if (edge < 0) {
     __syncthreads();                       // both read before they are written again
     return false;
   }
-  // The maxima in the k-th's bin and above, each decided once (a bit of a
-  // mask: the places a thread reserves are the ones it writes).
+  const int cap = min(slots / 2, kBinCap);
+  float thr = 0.f;
+  bool strict = false;
+  if (__builtin_expect(nq > min(k + kBinTied, cap), 0)) {
+    if (!est_refine(k, tm, n1, M, cap, sh, scale, edge, nq, thr, strict)) return false;
+  }
+  // The maxima in the k-th's bin and above (strict: above thr), each decided
+  // once, a bit of a mask: the places a thread reserves are the ones it writes.
   static_assert(4 * kBinMaxima4 <= 32, "a bit per maximum");
   const float fe = static_cast<float>(edge);
   unsigned in = 0;
-#pragma unroll
-  for (int u = 0; u < kBinMaxima4; ++u) {
-    if (u >= nu) break;
-    const float e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-    for (int c = 0; c < 4; ++c) in |= (est_bin_pos(e[c], M, scale) >= fe ? 1u : 0u) << (4 * u + c);
-  }
-  bool strict = false;
-  float thr = INFINITY;
-  if (nq > min(k + kBinTied, cap)) {
-    // Many at the edge.  If fewer than k maxima exceed the least of them, thr,
-    // that is the k-th, and only the tokens above it are wanted.
+  if (!strict) {
 #pragma unroll
     for (int u = 0; u < kBinMaxima4; ++u) {
       if (u >= nu) break;
       const float e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
-      for (int c = 0; c < 4; ++c) thr = in >> (4 * u + c) & 1u ? fminf(thr, e[c]) : thr;
+      for (int c = 0; c < 4; ++c) in |= (est_bin_pos(e[c], M, scale) >= fe ? 1u : 0u) << (4 * u + c);
     }
-    thr = -wave_max(-thr);
-    if (lane == 0) sh.fred[kEstMaxWaves + wave] = thr;
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kBinThreads / 64; ++i) thr = fminf(thr, sh.fred[kEstMaxWaves + i]);
-    unsigned gt = 0;
+  } else {
 #pragma unroll
     for (int u = 0; u < kBinMaxima4; ++u) {
       if (u >= nu) break;
       const float e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
-      for (int c = 0; c < 4; ++c) gt |= (e[c] > thr ? 1u : 0u) << (4 * u + c);
-    }
-    const int n_above = est_block_count(__popc(gt), sh);
-    if (n_above < k) {
-      strict = true;
-      in = gt;
-      nq = n_above;
-    } else if (nq > cap) {
-      return false;
+      for (int c = 0; c < 4; ++c) in |= (e[c] > thr ? 1u : 0u) << (4 * u + c);
     }
   }
   int total, o = est_block_offset(__popc(in), sh, total);
@@ -568,13 +584,25 @@ __device__ __forceinline__ bool est_binned(int est, int k, const float4 (&v)[kBi
   }
   static_assert(4 * kItems <= 32, "a bit per token");
   in = 0;
+  if (!strict) {
 #pragma unroll
-  for (int u = 0; u < kItems; ++u) {
-    if (u * kBinThreads >= 4 * nq) break;
+    for (int u = 0; u < kItems; ++u) {
+      if (u * kBinThreads >= 4 * nq) break;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      z[u][c] *= c2;
-      in |= ((strict ? z[u][c] > thr : est_bin_pos(z[u][c], M, scale) >= fe) ? 1u : 0u) << (4 * u + c);
+      for (int c = 0; c < 4; ++c) {
+        z[u][c] *= c2;
+        in |= (est_bin_pos(z[u][c], M, scale) >= fe ? 1u : 0u) << (4 * u + c);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < kItems; ++u) {
+      if (u * kBinThreads >= 4 * nq) break;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        z[u][c] *= c2;
+        in |= (z[u][c] > thr ? 1u : 0u) << (4 * u + c);
+      }
     }
   }
   o = est_block_offset(__popc(in), sh, total);
@@ -602,7 +630,7 @@ __device__ __forceinline__ bool est_binned(int est, int k, const float4 (&v)[kBi
   if (a < k) {
     theta = est_key(thr);                  // (strict: fewer than k tokens above the k-th maximum)
     if (t == 0) sh.rgt = a;
-  } else if (a <= kBinThreads) {
+  } else if (__builtin_expect(a <= kBinThreads, 1)) {
     // Each listed token counts those above it; the k-th largest is the least
     // token with fewer than k above it.
     unsigned least = 0xFFFFFFFFu;
@@ -709,23 +737,31 @@ __device__ __forceinline__ float row_estimate(int est, int k, const float* __res
   const float c2 = __fdiv_rn(kLog2e, T);
   if (k <= n1 && in_regs) {
     float H;
-    if (est_binned(est, k, v, n1, row, V, c2, est_key_slots(C, k), lds, sh, &H)) {
+    if (est_binned(est, k, v, tm, n1, row, V, c2, est_key_slots(C, k), lds, sh, &H)) {
       __syncthreads();                     // the LDS is the caller's again
       return H;
     }
   }
 
   // Stage 1: theta1 = k-th largest thread maximum (staged in LDS when the
-  // maxima fit).
+  // maxima fit, all of a thread's loads issued before its stores; loaded again
+  // if the bins were tried: registers held until here would lower the residency
+  // of the launches that share this code).
   const bool in_lds = n1 <= kEstLds1;
-  static_assert(kEstLds1 <= 4 * kBinMaxima4 * kBinThreads, "staged maxima are in registers");
   if (in_lds) {
+    constexpr int P4 = kEstLds1 / 4 / NT;            // float4 per thread, at most
+    float4 x[P4];
 #pragma unroll
-    for (int u = 0; u < kBinMaxima4; ++u) {
-      const int i4 = t + u * kBinThreads;
+    for (int u = 0; u < P4; ++u) {
+      const int i4 = t + u * NT;
+      x[u] = i4 < n1 / 4 ? reinterpret_cast<const float4*>(tm)[i4] : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+#pragma unroll
+    for (int u = 0; u < P4; ++u) {
+      const int i4 = t + u * NT;
       if (i4 < n1 / 4)
         reinterpret_cast<uint4*>(keys)[i4] =
-            make_uint4(est_key(v[u].x), est_key(v[u].y), est_key(v[u].z), est_key(v[u].w));
+            make_uint4(est_key(x[u].x), est_key(x[u].y), est_key(x[u].z), est_key(x[u].w));
     }
   }
   __syncthreads();
