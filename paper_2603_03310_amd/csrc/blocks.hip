@@ -44,7 +44,13 @@ constexpr int kThreads = 256;
 // and sums them in slot order.  Without the non-temporal bit 157.5 us at the
 // 8B shape, with it 138.4 with four tiles a wave, 141.5 with eight and 136.0
 // (5.56 TB/s) with two; before, with half the threads idle and each load
-// touching 256 B of four tiles, 155.7.
+// touching 256 B of four tiles, 155.7.  The bit also keeps the loads out of the
+// 256 MB last-level cache, for better or worse where the keys would fit it:
+// 128 MB of bf16 keys take 28 us against 33 with plain loads when they are not
+// in it (32 and 57 when it is full of other written data), 39 and 27 when they
+// were written just before.  No policy serves both, and the host cannot tell
+// them apart; keys of new prompts are larger than the cache, or older than what
+// the model wrote since, more often than not.
 constexpr int kSumTiles = 2;
 constexpr int kSumWaves = kThreads / 64;
 typedef unsigned sum_u32x4_t __attribute__((ext_vector_type(4)));

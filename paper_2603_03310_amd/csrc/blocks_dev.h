@@ -401,7 +401,7 @@ constexpr int kFoldThreads = 512;
 // The fold of virtual thread vt (head vt % H_q) over the nch tiles.  Up to
 // kFoldRegs tiles per virtual thread are loaded at once into registers; past
 // that they are taken that many at a time, the running pair rescaled once per
-// batch (16 sequences of 32768-131072 tokens: the tile launch 23.6 -> 16.8 us
+// batch (16 sequences of 32768-131072 tokens: the tile launch 23.6 -> 15.7 us
 // against two passes of one load a turn).
 constexpr int kFoldRegs = 16;
 __device__ __forceinline__ void lse_fold_vthread(const float* __restrict__ lse_part, int Hq,

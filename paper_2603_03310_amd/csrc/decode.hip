@@ -639,6 +639,9 @@ __global__ __launch_bounds__(kThreads, 3) void decode_bf16_kernel(DecodeArgs a) 
 // lane per whole dot product (48 lanes idle at G = 1), every weight formed in
 // every lane and no prefetch the launch took 8.5 us at the fp32 tiny step, so
 // 5.5; with the scoring in the entropy pass's launch the step 30.6 -> 23.2.
+// The widest form (G = 16, 128 dims) holds 266 registers, one workgroup per CU
+// where the earlier kernel had two, and the step of 4, 16 and 32 requests is
+// still 195 -> 74, 494 -> 226 and 1480 -> 725 us.
 template <int D, int G>
 __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
   constexpr int DPL = D / 64;     // dims per lane of the outputs
@@ -805,7 +808,12 @@ __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
 // and the 70B-shaped loop, few pieces a segment, are unchanged.  Every range
 // between the first and the last holds units, so all wrote a partial (testing
 // that cost two 64-bit divisions a piece: 2 us of the nine-request step's
-// 33.5, 9 us of 58 for two requests of 12465-25000 tokens).
+// 33.5, 9 us of 58 for two requests of 12465-25000 tokens).  Sixteen in flight
+// cost residency: 130 registers, three workgroups per CU, where eight had five
+// to seven.  No batch shows it: the launch takes 7.2 us at 128 requests of
+// the 70B shape, 9.0 at 200, 10.6 at 256 and 11.0 at 256 with 128 heads, with
+// eight 7.9, 9.5, 10.6 and 11.4; in 128 registers (four workgroups; indices
+// clamped for the branches) 10.4 at 256 and the long requests' 6.7 us became 7.5.
 constexpr int kCombinePrefetch = 16;       // partials whose loads are issued together
 
 // Ranges while the units are few: a workgroup per CU.  Where no more than that

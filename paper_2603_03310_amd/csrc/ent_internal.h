@@ -239,8 +239,11 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float x) {
 }
 
 // Cross-lane moves on the vector ALU (DPP within rows of 16 lanes, lane swaps
-// across them): the same values in the same order as shuffles through LDS, so
-// the same bits, without LDS latency at every step.  (A shuffle's result comes
+// across them), without LDS latency at every step.  The butterflies below add
+// in the order of shuffles and give their bits; the scans add whole rows of 16
+// lanes, where a scan by shuffles adds windows that cross them: the same for
+// integers, while the float64 sums of wave_scan_d (the sampler's) can differ
+// from such a scan's in their last bits.  (A shuffle's result comes
 // back after the LDS queue; six of them make one wave reduction, and the
 // selection, estimator and sampling bodies chain dozens.)  Against the shuffles:
 // sampling alone 17.6 -> 16.1 us, the fp32 tiny step 32.8 -> 31.1, one request

@@ -19,8 +19,9 @@
 //      ticket per sequence); sampling moves to D;
 //      Exact token-level scoring: A is the entropy pass and then the scoring
 //      pass over every key, B always the tile launch (block scores from that
-//      pass's pairs): five launches, the 8B step 295.5 us, where the staged
-//      calls in order (nine launches) took 304.4;
+//      pass's pairs): five launches, the 8B step 295 us, where the staged
+//      calls in order (nine launches) took 305;
+//   C  the decode attention over the kept blocks (decode.hip);
 //   D  the merge of split decode segments (and, on workgroups of their own,
 //      ent_decode_step_append's append of the new token's K/V and, for long
 //      block tables, the sampling).
