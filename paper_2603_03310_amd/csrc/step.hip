@@ -19,8 +19,8 @@
 //      ticket per sequence); sampling moves to D;
 //      Exact token-level scoring: A is the entropy pass and then the scoring
 //      pass over every key, B always the tile launch (block scores from that
-//      pass's pairs): five launches, the 8B step 295 us, where the staged
-//      calls in order (nine launches) took 305;
+//      pass's pairs): five launches, the 8B step 293 us, where the staged
+//      calls in order (nine launches) took 308;
 //   C  the decode attention over the kept blocks (decode.hip);
 //   D  the merge of split decode segments (and, on workgroups of their own,
 //      ent_decode_step_append's append of the new token's K/V and, for long
