@@ -6,7 +6,8 @@ long-table form's tile launch uses to pick each sequence's selecting
 workgroup return to zero by the end of every step, so a graph of the step
 replays exactly.  Two block-table forms: too wide for the one-launch
 selection (64 query heads, a 20000-token sequence: the tile launch with its
-per-sequence counters) and short enough for it.  The state the step changes
+per-sequence counters) and short enough for it; the same with exact scoring,
+with the estimators and with fp32 caches.  The state the step changes
 (controller and kept-fraction state, lengths, caches, block summaries) is
 restored and every output filled with a sentinel before the eager call and
 before every replay; between replays the program does eager work of its
@@ -15,7 +16,7 @@ own; every replay's outputs and state equal the eager step's.
 import numpy as np
 import pytest
 
-from synth import LLAMA3_8B, LLAMA70B_LOOP, default_params, generate, small
+from synth import LLAMA3_8B, LLAMA70B_LOOP, TINY, default_params, generate, small
 from synth.device import config_fields, upload
 from tests.test_gpu_parity import torch_cuda  # noqa: F401
 from tests.test_gpu_step_append import FIELDS, _host
@@ -25,7 +26,16 @@ pytestmark = pytest.mark.gpu
 CASES = [
     small(LLAMA70B_LOOP, 3, ctx=("fixed", [300, 20000, 9000]), steps=2, suffix="graph_wide"),
     small(LLAMA3_8B, 4, ctx=("fixed", [1, 300, 2000, 900]), steps=2, suffix="graph_short"),
+    # The exact mode's launches (tile launch and counters at every width), the
+    # estimators' in both forms, and the fp32 caches'.
+    small(LLAMA3_8B, 4, ctx=("fixed", [1, 300, 2000, 900]), steps=2, suffix="graph_exact"),
+    small(LLAMA70B_LOOP, 3, ctx=("fixed", [300, 20000, 9000]), steps=2, suffix="graph_exact_wide"),
+    small(LLAMA3_8B, 4, ctx=("fixed", [1, 300, 2000, 900]), steps=2, suffix="graph_tail"),
+    small(LLAMA70B_LOOP, 3, ctx=("fixed", [300, 20000, 9000]), steps=2, suffix="graph_topk_wide"),
+    small(TINY, 4, ctx=("fixed", [1, 300, 512, 90]), steps=2, suffix="graph_f32"),
 ]
+OPTIONS = {"exact": dict(scoring=1, keep_last=1), "exact_wide": dict(scoring=1, estimator=2),
+           "tail": dict(estimator=2), "topk_wide": dict(estimator=1, est_k=16)}
 STATE = ("h_prev", "tau", "temp", "kappa", "ctx_lens", "k_pool", "v_pool", "ksum")
 OUTPUTS = ("h", "temp_used", "row_stats", "kept", "n_kept", "scores", "theta", "out", "lse",
            "tokens")
@@ -67,7 +77,7 @@ def test_step_graph_replays_equal_eager(torch_cuda, w):
     torch = torch_cuda
     from paper_2603_03310_amd import ent
     from paper_2603_03310_amd.runner import Decoder
-    p = default_params(w).replace(dkappa=0.1)
+    p = default_params(w).replace(dkappa=0.1, **OPTIONS.get(w.name.split("graph_")[1], {}))
     x = generate(w)
     d = upload(x)
     print(f"[graph] {w.name}: blocks up to {w.max_blocks_per_seq}", flush=True)
